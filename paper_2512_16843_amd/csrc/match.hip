@@ -19,6 +19,7 @@
 // arg-max; the slot returned is then the best of those two groups, within that margin of the
 // true maximum, and the row is flagged (near-tie flag 2, counted separately) so that it is
 // reported rather than silently wrong.
+#include <algorithm>
 #include "common.h"
 #include "mma.h"
 
@@ -477,35 +478,85 @@ __global__ __launch_bounds__(512) void match_skew_kernel(
   }
 }
 
-// fp32 keys: plain FMA.  grid (B); thread t scans groups t, t + 256, ...
+// ---- fp32 keys, on the fp32 matrix instruction (16x16x4) ------------------------------------------
+// A workgroup of 4 wavefronts owns FN * 16 queries and a range of 128-row bank blocks, 32 rows per wavefront as two
+// 16-row fragments.  Operands come straight from memory: a lane fetches four consecutive k of one row (16 bytes at
+// k = 16 i + 4 (lane / 16)) and feeds one of them to each of four instructions, the same permutation of k on both
+// sides; the matrix work of 16 k (FN * 256 clocks of the SIMD) leaves the caches the time to deliver them.
+// Accumulators: col = lane % 16 is the query, register r of fragment f is bank row 16 f + 4 (lane / 16) + r, so the
+// lanes whose (lane / 16) has the same parity hold the 16 rows of one group between them.
+// What it replaces scanned the bank with one thread per group and one workgroup per query, a serial chain of 16 K
+// dependent loads: 375 us at 8 queries x 512 keys of 256, 10.6 us here (an empty launch is timed at 3.9).
+// grid (query blocks, n_split)
+template <int FN>
 __global__ __launch_bounds__(256) void match_f32_kernel(const float* __restrict__ bank,
                                                         const float* __restrict__ binv_eff, int N, int K,
-                                                        const float* __restrict__ queries, Top2* __restrict__ partial) {
-  extern __shared__ float sq[];    // [K] query, then Top2[256]
-  const int b = blockIdx.x;
-  for (int i = threadIdx.x; i < K; i += 256) sq[i] = queries[(size_t)b * K + i];
-  __syncthreads();
-  const int n_groups = ((N + 31) / 32) * 2;
-  Top2 t = top2_empty();
-  for (int g = threadIdx.x; g < n_groups; g += 256) {
-    float mx = NAN;
-    for (int r = 0; r < 16; ++r) {
-      const int row = group_row(g, r);
-      if (row >= N) continue;
-      const float* kp = bank + (size_t)row * K;
-      float a = 0.f;
-      for (int i = 0; i < K; ++i) a = fmaf(sq[i], kp[i], a);
-      mx = fmaxf(mx, a * binv_eff[row]);
+                                                        const float* __restrict__ queries, int B, int blocks_per_split,
+                                                        Top2* __restrict__ partial) {
+  __shared__ Top2 sc[4 * 2][FN * 16];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int l16 = lane & 15, quad = lane >> 4;
+  const int q0 = blockIdx.x * (FN * 16);
+  const int n_blocks = (N + 127) / 128;
+  const int b_begin = blockIdx.y * blocks_per_split, b_end = min(n_blocks, b_begin + blocks_per_split);
+  const float* qp[FN];
+#pragma unroll
+  for (int j = 0; j < FN; ++j) qp[j] = queries + (size_t)min(q0 + j * 16 + l16, B - 1) * K + quad * 4;
+  Top2 best[FN];
+#pragma unroll
+  for (int j = 0; j < FN; ++j) best[j] = top2_empty();
+  for (int blk = b_begin; blk < b_end; ++blk) {
+    const int rb = blk * 128 + wave * 32;
+    if (rb >= N) continue;
+    const float* kp[2];
+#pragma unroll
+    for (int f = 0; f < 2; ++f) kp[f] = bank + (size_t)min(rb + f * 16 + l16, N - 1) * K + quad * 4;
+    f32x4_t acc[2][FN];
+#pragma unroll
+    for (int f = 0; f < 2; ++f)
+#pragma unroll
+      for (int j = 0; j < FN; ++j) acc[f][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+    for (int k0 = 0; k0 < K; k0 += 32) {              // K is a multiple of 32; both halves are requested up front
+      f32x4_t fa[2][2], fb[2][FN];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+#pragma unroll
+        for (int f = 0; f < 2; ++f) fa[u][f] = *reinterpret_cast<const f32x4_t*>(kp[f] + k0 + u * 16);
+#pragma unroll
+        for (int j = 0; j < FN; ++j) fb[u][j] = *reinterpret_cast<const f32x4_t*>(qp[j] + k0 + u * 16);
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int f = 0; f < 2; ++f)
+#pragma unroll
+            for (int j = 0; j < FN; ++j)
+              acc[f][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[u][f][e], fb[u][j][e], acc[f][j], 0, 0, 0);
     }
-    top2_push(t, mx, g);
+    f32x4_t bi[2];                                    // NaN for free slots, and past N up to a multiple of 256
+#pragma unroll
+    for (int f = 0; f < 2; ++f) bi[f] = *reinterpret_cast<const f32x4_t*>(binv_eff + rb + f * 16 + quad * 4);
+    const int g = (rb >> 5) * 2 + (quad & 1);
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+      float mx = acc[0][j][0] * bi[0][0];
+#pragma unroll
+      for (int i = 1; i < 8; ++i) mx = fmaxf(mx, acc[i >> 2][j][i & 3] * bi[i >> 2][i & 3]);
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));         // the other eight rows of the group
+      top2_next(best[j], mx, g);                      // blocks ascend, so the lowest group stays among equals
+    }
   }
-  Top2* sc = reinterpret_cast<Top2*>(sq + K);
-  sc[threadIdx.x] = t;
+  if (lane < 32) {
+#pragma unroll
+    for (int j = 0; j < FN; ++j) sc[wave * 2 + quad][j * 16 + l16] = best[j];
+  }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    Top2 m = top2_empty();
-    for (int i = 0; i < 256; ++i) top2_merge(m, sc[i]);
-    partial[b] = m;
+  if (threadIdx.x < FN * 16 && q0 + (int)threadIdx.x < B) {
+    Top2 t = top2_empty();
+    for (int s = 0; s < 8; ++s) top2_merge(t, sc[s][threadIdx.x]);
+    partial[(size_t)blockIdx.y * B + q0 + threadIdx.x] = t;
   }
 }
 
@@ -617,6 +668,20 @@ static void split_plan(int N, int B, int* n_split, int* tiles_per_split) {
   *n_split = (tiles + per - 1) / per;
 }
 
+// fp32 keys: few queries take 16 per workgroup, more take 64 (a quarter of the bank reads per query)
+static int f32_query_block(int B) { return B <= 16 ? 16 : 64; }
+// about eight workgroups per compute unit; the splits are as few as keep the partial results within the fixed scratch
+// of llmc_match_noalloc, so that it takes every batch whose queries alone fit there
+static void f32_plan(int N, int B, int* n_split, int* blocks_per_split) {
+  const int blocks = (N + 127) / 128;
+  const int qb = (B + f32_query_block(B) - 1) / f32_query_block(B);
+  int want = std::min(std::min(blocks, 1024), std::max(1, 2048 / qb));
+  want = std::min(want, std::max(1, (int)(LLMC_MATCH_STATIC_SCRATCH_BYTES / sizeof(Top2) / (size_t)B)));
+  const int per = (blocks + want - 1) / want;
+  *blocks_per_split = per;
+  *n_split = (blocks + per - 1) / per;
+}
+
 // streaming kernel: about four workgroups per compute unit, at most 1024 splits
 static void stream_plan(int N, int B, int RB, int QB, int* n_qb, int* n_split, int* tiles_per_split) {
   const int tiles = (N + RB - 1) / RB;
@@ -644,6 +709,8 @@ size_t match_ws_bytes(int n_slots, int k, int dtype, int B) {
   if (dtype == LLMC_BF16) {
     if (use_stream(k)) stream_plan(n_slots, B, 64, stream_waves(B) * 64, &nqb, &ns, &per);
     else split_plan(n_slots, B, &ns, &per);
+  } else {
+    f32_plan(n_slots, B, &ns, &per);
   }
   return align_up((size_t)ns * B * sizeof(Top2), 256);
 }
@@ -733,10 +800,18 @@ llmc_status_t launch_match(const llmc_bank* bank, const void* d_fp, const float*
                        (const bf16_t*)D.d_fp, D.d_inv_norm, D.d_valid, N, K, (const bf16_t*)d_fp, d_inv, B, tau, d_idx,
                        d_sim, d_hit, d_near_tie); }
   } else {
-    { ProfScope ps_("match_f32_kernel", st); LLMC_KERNEL_GGL(match_f32_kernel, dim3(B), dim3(256), (size_t)K * sizeof(float) + 256 * sizeof(Top2), st,
-                       (const float*)D.d_fp, bank->d_binv_eff, N, K, (const float*)d_fp, partial); }
+    f32_plan(N, B, &ns, &per);
+    const int qblock = f32_query_block(B);
+    const dim3 grid((B + qblock - 1) / qblock, ns);
+    { ProfScope ps_("match_f32_kernel", st);
+      if (qblock == 16)
+        LLMC_KERNEL_GGL(match_f32_kernel<1>, grid, dim3(256), 0, st, (const float*)D.d_fp, bank->d_binv_eff, N, K,
+                        (const float*)d_fp, B, per, partial);
+      else
+        LLMC_KERNEL_GGL(match_f32_kernel<4>, grid, dim3(256), 0, st, (const float*)D.d_fp, bank->d_binv_eff, N, K,
+                        (const float*)d_fp, B, per, partial); }
     LLMC_LAUNCH_CHECK("match_f32_kernel");
-    { ProfScope ps_("match_finalize_kernel", st); LLMC_KERNEL_GGL((match_finalize_kernel<float>), dim3((B + 3) / 4), dim3(256), 0, st, partial, 1,
+    { ProfScope ps_("match_finalize_kernel", st); LLMC_KERNEL_GGL((match_finalize_kernel<float>), dim3((B + 3) / 4), dim3(256), 0, st, partial, ns,
                        (const float*)D.d_fp, D.d_inv_norm, D.d_valid, N, K, (const float*)d_fp, d_inv, B, tau, d_idx,
                        d_sim, d_hit, d_near_tie); }
   }

@@ -17,6 +17,7 @@ namespace llmc {
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef float f32x16_t __attribute__((ext_vector_type(16)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
 
 // row of register r of a 32x32 accumulator fragment held by `lane`
 __device__ __forceinline__ int frag_row(int lane, int r) { return (lane >> 5) * 4 + 8 * (r >> 2) + (r & 3); }

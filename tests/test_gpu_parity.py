@@ -375,6 +375,23 @@ def test_match_f32(L):
     bank.close()
 
 
+@pytest.mark.parametrize("N,B,k", [(1, 1, 32), (31, 3, 64), (129, 16, 96), (1000, 17, 256), (4097, 70, 128),
+                                   (300, 65, 1024)])
+def test_match_f32_edges(L, N, B, k):
+    """Sizes around the 32-row fragments, the 128-row blocks and the two query blockings (16 and 64)."""
+    say("match f32 N=%d B=%d k=%d with holes" % (N, B, k))
+    g = np.random.Generator(np.random.PCG64(1000 + N))
+    keys = torch.from_numpy(unit_rows(g, N, k).astype(np.float32)).cuda()
+    valid = g.random(N) > 0.2
+    valid[N // 2] = True
+    bank = make_bank(L, keys, torch.from_numpy(valid.astype(np.uint8)), dtype=torch.float32)
+    qn = unit_rows(g, B, k)
+    near = np.nonzero(valid)[0][-min(B, int(valid.sum())):]
+    qn[:len(near)] = npf(keys)[near] + 0.01 * g.standard_normal((len(near), k))
+    check_match(L, bank, torch.from_numpy(qn.astype(np.float32)).cuda(), 0.9, "f32")
+    bank.close()
+
+
 def test_match_clustered_bank_scaled_stress(L):
     say("match bf16 clustered bank 128 clusters x 256, 1024 queries (scaled copy of the stress config)")
     data = W.make_clustered_bank(128, 256, 256, 0.05, 1024, seed=5)

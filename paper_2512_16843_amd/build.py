@@ -10,7 +10,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libllmc.so")
 SOURCES = ["api.hip", "fingerprint.hip", "match.hip", "bits.hip", "lsh.hip", "gate.hip", "bank.hip", "layer.hip",
-           "attention.hip"]
+           "dense_f32.hip", "attention.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-Wall", "-Wno-unused-function",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 # the attention kernel feeds every matrix-instruction result to vector instructions at once: accumulators in VGPRs,

@@ -50,6 +50,9 @@ struct GemmArgs {
   int xcd_chunks;                  // tile -> workgroup map of the direct-to-LDS kernel, see there
 };
 
+// the fp32 form (dense_f32.hip)
+llmc_status_t launch_gemm_f32(const GemmArgs& g, hipStream_t st);
+
 __device__ __forceinline__ float apply_act(float v, int act) {
   if (act == 1) return gelu_erf(v);
   if (act == 2) return gelu_tanh(v);

@@ -7,8 +7,8 @@
 // beyond it exit at once, so the host never learns the number of misses.
 //
 // Kernels: linear layers on the bf16 matrix cores (fp32 accumulate) with bias, GELU,
-// residual and row gather/scatter fused into the epilogue; a plain fp32 FMA GEMM for
-// fp32 runs; LayerNorm with one wavefront per token (the last LayerNorm of a post-LN block
+// residual and row gather/scatter fused into the epilogue (those of fp32 runs are a
+// translation unit of their own); LayerNorm with one wavefront per token (the last LayerNorm of a post-LN block
 // also leaves the pooled chunk sums of the rows it writes for the next fingerprint); the
 // fp32 softmax attention with one thread per query row.  The bf16 attention on the matrix
 // cores is a translation unit of its own.
@@ -24,62 +24,6 @@ typedef MmaCfg<128, 128, 32, 2, 2> GemmCfg;
 // their tiles / rows with a grid stride and read the real count on the device, so a layer
 // with few or no misses costs a small, fixed number of idle workgroups.
 constexpr int kMaxGrid = 512;
-
-// ---- fp32 GEMM, plain FMA: 64x64 tile, 16-wide k step, 4x4 outputs per thread ------------------
-__global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgs g, int tiles_n) {
-  __shared__ float sA[16][64 + 4];
-  __shared__ float sB[16][64 + 4];
-  const int n_seq = g.count ? min(*g.count, g.max_seqs) : g.max_seqs;
-  const int M = n_seq * g.S;
-  const int tile_m = blockIdx.x / tiles_n, tile_n = blockIdx.x % tiles_n;
-  const int m0 = tile_m * 64, n0 = tile_n * 64;
-  if (m0 >= M) return;
-  const int tid = threadIdx.x;
-  const float* A = (const float*)g.A;
-  const float* W = (const float*)g.W;
-  // each thread loads one float4 of A and one of W per k step: row = tid / 4, k = (tid % 4) * 4
-  const int lr = tid >> 2, lk = (tid & 3) * 4;
-  const float* ap = A + map_row(g.a_rows, min(m0 + lr, M - 1), g.S) * g.lda + lk;
-  const float* wp = W + (size_t)min(n0 + lr, g.N - 1) * g.K + lk;
-  const int tm = (tid >> 4) * 4, tn = (tid & 15) * 4;
-  float acc[4][4] = {};
-  for (int k0 = 0; k0 < g.K; k0 += 16) {
-    const float4 va = *reinterpret_cast<const float4*>(ap + k0);
-    const float4 vw = *reinterpret_cast<const float4*>(wp + k0);
-    sA[lk + 0][lr] = va.x; sA[lk + 1][lr] = va.y; sA[lk + 2][lr] = va.z; sA[lk + 3][lr] = va.w;
-    sB[lk + 0][lr] = vw.x; sB[lk + 1][lr] = vw.y; sB[lk + 2][lr] = vw.z; sB[lk + 3][lr] = vw.w;
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) {
-      float a[4], b[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) { a[i] = sA[kk][tm + i]; b[i] = sB[kk][tn + i]; }
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(a[i], b[j], acc[i][j]);
-    }
-    __syncthreads();
-  }
-  const float* bias = (const float*)g.bias;
-  const float* resid = (const float*)g.resid;
-  float* out = (float*)g.out;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int m = m0 + tm + i;
-    if (m >= M) continue;
-    const int64_t ro = map_row(g.o_rows, m, g.S) * g.ldo;
-    const int64_t rr = resid ? map_row(g.r_rows, m, g.S) * g.ldr : 0;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int n = n0 + tn + j;
-      if (n >= g.N) continue;
-      float v = apply_act(acc[i][j] + (bias ? bias[n] : 0.f), g.act);
-      if (resid) v += resid[rr + n];
-      out[ro + n] = v;
-    }
-  }
-}
 
 // 128 x 128 block, 8 wavefronts (2 x 4), two 64-column stages filled by direct-to-LDS loads: 68 KiB of LDS,
 // so two workgroups share a compute unit and one's epilogue overlaps the other's main loop
@@ -112,10 +56,7 @@ static llmc_status_t launch_gemm(const GemmArgs& g, int dtype, hipStream_t st) {
                          0, st, g, tiles_n);
     }
   } else {
-    const int tiles_n = (g.N + 63) / 64;
-    const int tiles_m = (g.max_seqs * g.S + 63) / 64;
-    ProfScope ps_("gemm_f32_kernel", st);
-    LLMC_KERNEL_GGL(gemm_f32_kernel, dim3((unsigned)tiles_m * tiles_n), dim3(256), 0, st, g, tiles_n);
+    return launch_gemm_f32(g, st);
   }
   LLMC_LAUNCH_CHECK("gemm");
   return LLMC_OK;

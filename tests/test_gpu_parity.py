@@ -1779,6 +1779,37 @@ def test_few_rows_and_many_rows_give_the_same_bits(L, arch):
     big.close()
 
 
+@pytest.mark.parametrize("d,dff,S,B", [
+    (64, 64, 1, 1),          # one token, one column tile
+    (192, 320, 33, 3),       # 99 tokens: ragged against 32 and 64 rows, widths that are odd multiples of 64
+    (768, 3072, 128, 12),    # 1536 tokens: the feed-forward layers take the wide tiles, the others the small ones
+])
+@pytest.mark.parametrize("arch", [0, 1])
+def test_f32_layer_tilings(L, arch, d, dff, S, B):
+    """The fp32 block on its tilings against the oracle, and the same bits for the last sequence computed alone."""
+    from paper_2512_16843_amd.engine import GatedStack
+    say(f"plain fp32 layer arch={arch} d={d} dff={dff} S={S} B={B}")
+    cfg = small_cfg(arch, "f32", d, d // 64, dff, S, B)
+    ws = W.make_layer_weights(cfg, seed=12)
+    Ps = W.make_projection(d, cfg.k, torch.float32)
+    g = np.random.Generator(np.random.PCG64(d + S))
+    h0 = torch.from_numpy(g.standard_normal((B, S, d)).astype(np.float32)).cuda()
+    st = GatedStack(cfg, ws, Ps, cached_layers=[])
+    out = st.forward(h0, tau=0.5).clone()
+    torch.cuda.synchronize()
+    one = GatedStack(W.scaled(cfg, B=1), ws, Ps, cached_layers=[])
+    alone = one.forward(h0[B - 1:].contiguous(), tau=0.5)
+    torch.cuda.synchronize()
+    assert torch.equal(alone[0], out[B - 1])
+    wnp = {k: npf(v) for k, v in ws[0].items()}
+    rows = [0, B - 1]
+    want = np.stack([O.layer_forward(npf(h0[b]), wnp, arch, d // 64, cfg.ln_eps, cfg.gelu) for b in rows])
+    # sums of at most 3072 fp32 products per element, a few layers of them: well inside 1e-5 of the row's largest value
+    assert rel_err_rows(npf(out)[rows], want).max() < 1e-5
+    st.close()
+    one.close()
+
+
 @pytest.mark.parametrize("carry", [False, True], ids=["plain", "carried"])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_within_batch_reuse_against_oracle(L, dtype, carry):

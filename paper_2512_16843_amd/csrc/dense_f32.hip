@@ -32,14 +32,17 @@ struct F32Cfg {
   static constexpr size_t LDS_BYTES = (size_t)STAGES * STAGE * 4;
   static_assert(BM % 32 == 0 && BN % 32 == 0 && (STAGES - 2) * L <= 15, "tiling");
 };
-typedef F32Cfg<64, 64, 3> F32Wide;     // 48 KiB: three workgroups per compute unit
-typedef F32Cfg<32, 32, 5> F32Small;    // 40 KiB
+// 32 KiB either way, so that five workgroups share a compute unit and hide each other's waits: deeper rings (48 and
+// 40 KiB, three workgroups) are 2-8 % slower from 512 to 4096 rows, a three-stage small ring 5 % at 128 rows.
+typedef F32Cfg<64, 64, 2> F32Wide;
+typedef F32Cfg<32, 32, 4> F32Small;
 
-// At most this many 64 x 64 tiles: the launch is cut into 32 x 32 tiles.  A 64 x 64 tile keeps a SIMD busy for four
-// times as long, so with fewer than about four tiles per compute unit the last round of them leaves most of the chip
-// idle.  512 rows of the 768-wide block: 48 us per layer with small tiles, 83 us with wide ones; at 8192 rows wide
-// ones read half the bytes per flop.
-constexpr int kF32SmallTiles = 1024;
+// At most this many 64 x 64 tiles: the launch is cut into 32 x 32 tiles.  A 64 x 64 tile keeps its SIMDs busy four times
+// as long, so with two tiles or fewer per compute unit the last round of them leaves much of the chip idle; beyond
+// that the wide tiles' halved operand traffic wins.  The four linear layers of a 768-wide block, small / wide: 62 / 124 us
+// at 128 rows, 106 / 152 at 512, 156 (the line) / 183 at 1024; 589 (all below 1024 tiles small) / 514 at 4096, where
+// they reach 113 TFLOP/s.
+constexpr int kF32SmallTiles = 640;
 constexpr int kF32MaxGrid = 1024;
 
 template <class C>

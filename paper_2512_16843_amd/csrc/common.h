@@ -270,6 +270,8 @@ llmc_status_t launch_linear(const void* A, int lda, const int32_t* a_rows, const
 // bf16 softmax attention on the matrix cores (head size 64): qkv [T, 3d] -> ctx [T, d]; sequences beyond *count skipped
 llmc_status_t launch_attention_bf16(const void* qkv, void* ctx, int S, int d, int n_heads, bool causal,
                                     const int32_t* count, int max_seqs, hipStream_t st);
+llmc_status_t launch_attention_f32(const void* qkv, void* ctx, int S, int d, int n_heads, bool causal, const int32_t* count,
+                                   int max_seqs, hipStream_t st);      // the same in fp32
 // Section IV-B, prefix attention statistics: the block's self-attention sub-layer run over the first n_prefix tokens of
 // every sequence alone; the mean of its outputs over those tokens goes to out[b * ld_out ..] [d] fp32
 size_t prefix_attention_ws_bytes(const llmc_layer_desc_t* L, int B, int n_prefix);

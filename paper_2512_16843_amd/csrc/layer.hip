@@ -7,11 +7,10 @@
 // beyond it exit at once, so the host never learns the number of misses.
 //
 // Kernels: linear layers on the bf16 matrix cores (fp32 accumulate) with bias, GELU,
-// residual and row gather/scatter fused into the epilogue (those of fp32 runs are a
-// translation unit of their own); LayerNorm with one wavefront per token (the last LayerNorm of a post-LN block
-// also leaves the pooled chunk sums of the rows it writes for the next fingerprint); the
-// fp32 softmax attention with one thread per query row.  The bf16 attention on the matrix
-// cores is a translation unit of its own.
+// residual and row gather/scatter fused into the epilogue; LayerNorm with one wavefront per
+// token (the last LayerNorm of a post-LN block also leaves the pooled chunk sums of the rows
+// it writes for the next fingerprint).  The two attention kernels and the linear layers of
+// fp32 runs are translation units of their own.
 #include "common.h"
 #include <algorithm>
 #include "gemm.h"
@@ -277,97 +276,12 @@ static llmc_status_t launch_ln_pool(const void* in, void* out, const int32_t* ou
   return LLMC_OK;
 }
 
-// ---- attention: one thread per query row, online softmax over 32-key tiles ------------------------
-// qkv [T, 3d] compact; ctx [T, d] compact.  grid (ceil(S / 128), heads, max_seqs).
-template <typename T, bool CAUSAL>
-__global__ __launch_bounds__(128) void attention_kernel(const T* __restrict__ qkv, T* __restrict__ ctx, int S, int d,
-                                                        float scale, const int32_t* count, int max_seqs) {
-  constexpr int DH = 64, KT = 32, VEC = Vec16<T>::N;
-  __shared__ __attribute__((aligned(16))) float sK[KT][DH];
-  __shared__ __attribute__((aligned(16))) float sV[KT][DH];
-  const int n_seq = count ? min(*count, max_seqs) : max_seqs;
-  const int seq = blockIdx.z;
-  if (seq >= n_seq) return;
-  const int head = blockIdx.y;
-  const int q0 = blockIdx.x * 128;
-  const int qi = q0 + threadIdx.x;
-  const int qrow = min(qi, S - 1);
-  const size_t ld = 3 * (size_t)d;
-  const T* base = qkv + (size_t)seq * S * ld + head * DH;
-  float q[DH], o[DH];
-#pragma unroll
-  for (int c = 0; c < DH; c += VEC) Vec16<T>::load(base + (size_t)qrow * ld + c, &q[c]);
-#pragma unroll
-  for (int c = 0; c < DH; ++c) o[c] = 0.f;
-  float m = -INFINITY, l = 0.f;
-  const int kv_end = CAUSAL ? min(S, q0 + 128) : S;
-  for (int k0 = 0; k0 < kv_end; k0 += KT) {
-    __syncthreads();
-    for (int v = threadIdx.x; v < KT * DH / VEC; v += 128) {
-      const int j = v / (DH / VEC), c = (v % (DH / VEC)) * VEC;
-      const int kr = min(k0 + j, S - 1);
-      Vec16<T>::load(base + (size_t)kr * ld + d + c, &sK[j][c]);
-      Vec16<T>::load(base + (size_t)kr * ld + 2 * d + c, &sV[j][c]);
-    }
-    __syncthreads();
-    float s[KT];
-    float tmax = -INFINITY;
-#pragma unroll
-    for (int j = 0; j < KT; ++j) {
-      float a = 0.f;
-#pragma unroll
-      for (int c = 0; c < DH; ++c) a = fmaf(q[c], sK[j][c], a);
-      a *= scale;
-      const int kv = k0 + j;
-      if (kv >= S || (CAUSAL && kv > qrow)) a = -INFINITY;
-      s[j] = a;
-      tmax = fmaxf(tmax, a);
-    }
-    const float m_new = fmaxf(m, tmax);
-    if (m_new == -INFINITY) continue;   // nothing visible yet in this tile (cannot happen for kv 0)
-    const float corr = __expf(m - m_new);
-    l *= corr;
-#pragma unroll
-    for (int c = 0; c < DH; ++c) o[c] *= corr;
-#pragma unroll
-    for (int j = 0; j < KT; ++j) {
-      const float p = __expf(s[j] - m_new);
-      l += p;
-#pragma unroll
-      for (int c = 0; c < DH; ++c) o[c] = fmaf(p, sV[j][c], o[c]);
-    }
-    m = m_new;
-  }
-  if (qi < S) {
-    const float inv = 1.0f / l;
-    T* dst = ctx + ((size_t)seq * S + qi) * d + head * DH;
-#pragma unroll
-    for (int c = 0; c < DH; c += VEC) {
-      float y[VEC];
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) y[e] = o[c + e] * inv;
-      Vec16<T>::store(dst + c, y);
-    }
-  }
-}
-
+// ---- attention (translation units of their own) ------------------------------------------------------
 template <typename T>
 static llmc_status_t launch_attention(const void* qkv, void* ctx, int S, int d, int n_heads, bool causal,
                                       const int32_t* count, int max_seqs, hipStream_t st) {
-  const float scale = 1.0f / sqrtf((float)(d / n_heads));
   if (sizeof(T) == 2) return launch_attention_bf16(qkv, ctx, S, d, n_heads, causal, count, max_seqs, st);
-  {
-    dim3 grid((S + 127) / 128, n_heads, max_seqs);
-    ProfScope ps_("attention_kernel", st);
-    if (causal)
-      LLMC_KERNEL_GGL((attention_kernel<T, true>), grid, dim3(128), 0, st, (const T*)qkv, (T*)ctx, S, d, scale, count,
-                         max_seqs);
-    else
-      LLMC_KERNEL_GGL((attention_kernel<T, false>), grid, dim3(128), 0, st, (const T*)qkv, (T*)ctx, S, d, scale,
-                         count, max_seqs);
-  }
-  LLMC_LAUNCH_CHECK("attention");
-  return LLMC_OK;
+  return launch_attention_f32(qkv, ctx, S, d, n_heads, causal, count, max_seqs, st);
 }
 
 // ---- the block -----------------------------------------------------------------------------------

@@ -1782,6 +1782,7 @@ def test_few_rows_and_many_rows_give_the_same_bits(L, arch):
 @pytest.mark.parametrize("d,dff,S,B", [
     (64, 64, 1, 1),          # one token, one column tile
     (192, 320, 33, 3),       # 99 tokens: ragged against 32 and 64 rows, widths that are odd multiples of 64
+    (128, 64, 145, 2),       # attention: two query blocks and a third of 17, five key tiles, the last with 17 keys
     (768, 3072, 128, 12),    # 1536 tokens: the feed-forward layers take the wide tiles, the others the small ones
 ])
 @pytest.mark.parametrize("arch", [0, 1])

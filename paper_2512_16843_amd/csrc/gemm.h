@@ -1,6 +1,7 @@
 // Linear layer  out = act(A * W^T + bias) (+ residual)  on the bf16 matrix cores, with the
 // row gather / scatter of the miss path fused into operand loads and the epilogue.
 #pragma once
+#include <type_traits>
 #include "common.h"
 #include "mma.h"
 
@@ -202,9 +203,158 @@ __device__ __forceinline__ void gemm_epilogue_wave16(const GemmArgs& g, f32x16_t
 
 template <class C, class CS>
 constexpr size_t gemm_dma_smem_bytes() {
-  return C::LDS_BYTES > CS::LDS_BYTES ? C::LDS_BYTES : CS::LDS_BYTES;
+  return C::LDS_BYTES > CS::LDS_BYTES ? C::LDS_BYTES : CS::LDS_BYTES;   // GemmFew: as much as CS
 }
 
+// ---- a handful of rows ---------------------------------------------------------------------------
+// With few rows a launch is one pass over k by a few workgroups and its time is the latency of the loads over the
+// number of steps in flight.  So: 32 x 64 tiles (four times the workgroups of 64 x 128, each a quarter of the work
+// of its compute unit) and a ring of six 12 KiB stages, five steps of 64 k ahead, in the LDS of the launch.  All
+// eight wavefronts load (a stage is twelve blocks of eight rows: wavefronts 0..3 fetch two, the others one), the first
+// two multiply, one 32 x 32 fragment each.  An element is accumulated over k in the order of the other tilings.
+// At 128 rows of a 768-wide block (64 x 128 tiles with three stages before): QKV 8.0 -> 5.5 us, output projection 8.1 ->
+// 5.9, feed-forward 9.1 -> 6.9 and 20.0 -> 11.1, of which an empty launch is 4.  The loop below matters as much as the
+// tile: with every fragment read waited for before its own multiply the last of them took 23.4 us.
+struct GemmFew {
+  static constexpr int BM = 32, BN = 64, BK = 64, STAGES = 6;
+  static constexpr int STAGE_ELEMS = (BM + BN) * BK;
+  static constexpr size_t LDS_BYTES = (size_t)STAGES * STAGE_ELEMS * 2;
+};
+
+// The k loop of one wavefront: PER loads a step; COMPUTE: it multiplies too.  The fragments of step kt are read from LDS
+// behind the multiplies of step kt - 1 that free their registers, so a step does not cost the sum of the two.
+template <int PER, bool COMPUTE>
+__device__ __forceinline__ void gemm_few_loop(const uint16_t* p0, const uint16_t* p1, int nk, int wave, uint16_t* lds,
+                                              int a_row, int b_row, const int (&sw)[4], f32x16_t& acc) {
+  using C = GemmFew;
+  int in = 0, rd = 0;                                        // ring stages of the next load and of the next read
+  auto issue = [&](int kt) {
+    uint16_t* st = lds + in * C::STAGE_ELEMS;
+    in = in + 1 == C::STAGES ? 0 : in + 1;
+    __builtin_amdgcn_global_load_lds(LLMC_GPTR(p0 + kt * C::BK), LLMC_LPTR(st + wave * 8 * C::BK), 16, 0, 0);
+    if (PER == 2)
+      __builtin_amdgcn_global_load_lds(LLMC_GPTR(p1 + kt * C::BK), LLMC_LPTR(st + (8 + wave) * 8 * C::BK), 16, 0, 0);
+  };
+  bf16x8_t fa[4], fb[4];                                     // zeros until the first step has been read
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) fa[ks] = fb[ks] = bf16x8_t{};
+  // everybody's loads of this step have landed, and everybody has its fragments of the step before
+  auto step = [&](int kt, bool more) {
+    if (COMPUTE) LLMC_WAIT_LGKM(0);
+    dma::barrier();
+    if (more) issue(kt + C::STAGES - 1);
+    if (COMPUTE) {
+      const uint16_t* st = lds + rd * C::STAGE_ELEMS;
+      rd = rd + 1 == C::STAGES ? 0 : rd + 1;
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks], fb[ks], acc, 0, 0, 0);
+        fa[ks] = *reinterpret_cast<const bf16x8_t*>(st + a_row + sw[ks]);
+        fb[ks] = *reinterpret_cast<const bf16x8_t*>(st + b_row + sw[ks]);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    }
+  };
+  for (int s = 0; s < C::STAGES - 1; ++s)
+    if (s < nk) issue(s);
+  int kt = 0;
+  for (; kt + C::STAGES - 1 < nk; ++kt) {
+    LLMC_WAIT_VM((C::STAGES - 2) * PER);
+    step(kt, true);
+  }
+  auto tail = [&](auto steps) {
+    constexpr int ahead = decltype(steps)::value;
+    if (kt == nk - 1 - ahead) {                              // not for every one when nk < STAGES - 1
+      LLMC_WAIT_VM(ahead * PER);
+      step(kt, false);
+      ++kt;
+    }
+  };
+  static_assert(C::STAGES == 6, "the steps of the tail");
+  tail(std::integral_constant<int, 4>());
+  tail(std::integral_constant<int, 3>());
+  tail(std::integral_constant<int, 2>());
+  tail(std::integral_constant<int, 1>());
+  tail(std::integral_constant<int, 0>());
+  if (COMPUTE) {
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks], fb[ks], acc, 0, 0, 0);
+  }
+}
+
+__device__ __forceinline__ void gemm_few_tiles(const GemmArgs& g, int M, int total, int tiles_n, uint16_t* lds) {
+  using C = GemmFew;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const uint16_t* A = (const uint16_t*)g.A;
+  const uint16_t* W = (const uint16_t*)g.W;
+  const uint16_t* bias = (const uint16_t*)g.bias;
+  const uint16_t* resid = (const uint16_t*)g.resid;
+  uint16_t* out = (uint16_t*)g.out;
+  const int nk = g.K / C::BK;
+  int sw[4];
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) sw[ks] = (((ks * 2 + (lane >> 5)) ^ ((lane >> 1) & 7)) * 8);
+  const int a_row = (lane & 31) * C::BK;
+  const int b_row = (C::BM + wave * 32 + (lane & 31)) * C::BK;          // of the multiplying wavefronts
+  for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
+    const int m0 = (tile / tiles_n) * C::BM, n0 = (tile % tiles_n) * C::BN;
+    // block `wave` of a stage, and block 8 + wave for wavefronts 0..3: blocks 0..3 are rows of A, 4..11 rows of W
+    auto source = [&](int block) -> const uint16_t* {
+      const int tr = block * 8 + (lane >> 3);
+      const int chunk = ((lane & 7) ^ ((tr >> 1) & 7)) * 8;
+      if (block < 4) return A + map_row(g.a_rows, min(m0 + tr, M - 1), g.S) * g.lda + chunk;
+      return W + (size_t)min(n0 + tr - C::BM, g.N - 1) * g.K + chunk;
+    };
+    const uint16_t* p0 = source(wave);
+    const uint16_t* p1 = wave < 4 ? source(8 + wave) : p0;
+    f32x16_t acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    if (wave < 2) gemm_few_loop<2, true>(p0, p1, nk, wave, lds, a_row, b_row, sw, acc);
+    else if (wave < 4) gemm_few_loop<2, false>(p0, p1, nk, wave, lds, a_row, b_row, sw, acc);
+    else gemm_few_loop<1, false>(p0, p1, nk, wave, lds, a_row, b_row, sw, acc);
+    dma::barrier();               // every fragment has been read: the first stage takes the staging of the epilogue
+    if (wave < 2) {
+      // 32 x 32 fp32 laid out by row, then four lanes take a row each, 8 consecutive columns a lane
+      float* region = reinterpret_cast<float*>(lds) + wave * 32 * 36;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) region[frag_row(lane, r) * 36 + (lane & 31)] = acc[r];
+      const int c8 = (lane & 3) * 8, n = n0 + wave * 32 + c8;
+      float bv[8];
+#pragma unroll
+      for (int e = 0; e < 8; ++e) bv[e] = 0.f;
+      if (bias && n < g.N) Vec16<bf16_t>::load(reinterpret_cast<const bf16_t*>(bias + n), bv);
+#pragma unroll
+      for (int pass = 0; pass < 2; ++pass) {
+        const int row = pass * 16 + (lane >> 2), m = m0 + row;
+        const float4 lo = *reinterpret_cast<const float4*>(region + row * 36 + c8);
+        const float4 hi = *reinterpret_cast<const float4*>(region + row * 36 + c8 + 4);
+        if (m < M && n < g.N) {
+          float v[8] = {lo.x + bv[0], lo.y + bv[1], lo.z + bv[2], lo.w + bv[3],
+                        hi.x + bv[4], hi.y + bv[5], hi.z + bv[6], hi.w + bv[7]};
+          if (g.act) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = apply_act(v[e], g.act);
+          }
+          if (resid) {
+            float rr[8];
+            Vec16<bf16_t>::load(reinterpret_cast<const bf16_t*>(resid + map_row(g.r_rows, m, g.S) * g.ldr + n), rr);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] += rr[e];
+          }
+          Vec16<bf16_t>::store(reinterpret_cast<bf16_t*>(out + map_row(g.o_rows, m, g.S) * g.ldo + n), v);
+        }
+      }
+    }
+    dma::barrier();               // ... and is read out before the next tile's first loads land there
+  }
+}
+
+// At most this many 32 x 64 tiles in a launch: all of them are resident at once (two workgroups per compute unit).  788
+// rows: 300 tiles of a 768-wide output take 8.0 (K = 768) and 17.2 us (K = 3072) against 8.7 and 20.2 as 78 tiles of
+// 64 x 128; wider outputs at those rows (900 and 1200 tiles) stay with the larger tiles.
+constexpr int kGemmFewTiles = 512;
 // at most this many C tiles in a launch: the launch takes CS tiles instead (see the kernel)
 constexpr int kGemmSmallTiles = 256;
 
@@ -219,7 +369,7 @@ constexpr int kGemmSmallTiles = 256;
 // its compute unit to itself spends a step waiting for that step's loads.  An output element is accumulated over k
 // in the same order by either tiling, so the bits of a row do not depend on how many rows are computed with it.
 template <class C, class CS>
-__global__ __launch_bounds__(C::THREADS) void gemm_bf16_dma_kernel(GemmArgs g, int tiles_n) {
+__global__ __launch_bounds__(C::THREADS, 4) void gemm_bf16_dma_kernel(GemmArgs g, int tiles_n) {
   static_assert(C::THREADS == CS::THREADS && C::BN == CS::BN, "the two tilings share the launch shape and the column tiles");
   extern __shared__ __attribute__((aligned(16))) uint16_t lds_dyn[];
   const int n_seq = g.count ? min(*g.count, g.max_seqs) : g.max_seqs;
@@ -228,6 +378,11 @@ __global__ __launch_bounds__(C::THREADS) void gemm_bf16_dma_kernel(GemmArgs g, i
   const int total = tiles_m * tiles_n;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   if (total <= kGemmSmallTiles) {
+    const int few_n = (g.N + GemmFew::BN - 1) / GemmFew::BN, few = ((M + GemmFew::BM - 1) / GemmFew::BM) * few_n;
+    if (few <= kGemmFewTiles) {
+      gemm_few_tiles(g, M, few, few_n, lds_dyn);
+      return;
+    }
     const int total_s = ((M + CS::BM - 1) / CS::BM) * tiles_n;
     const uint16_t* A = (const uint16_t*)g.A;
     const uint16_t* W = (const uint16_t*)g.W;

@@ -40,12 +40,14 @@ static llmc_status_t launch_gemm(const GemmArgs& g, int dtype, hipStream_t st) {
       const size_t lds_bytes = gemm_dma_smem_bytes<C, CS>();
       LLMC_TRY(ensure_dynamic_lds((const void*)kernel, lds_bytes, lds_set));
       const int tiles_n = (g.N + C::BN - 1) / C::BN;
-      // the grid covers the smaller tiling too, which the kernel takes when the rows it finds on the device are few
+      // the grid covers the smaller tilings too, which the kernel takes when the rows it finds on the device are few
+      static_assert(GemmFew::LDS_BYTES <= gemm_dma_smem_bytes<C, CS>(), "the stages of every tiling fit the launch");
       const int tiles_m = (g.max_seqs * g.S + CS::BM - 1) / CS::BM;
+      const int few = ((g.max_seqs * g.S + GemmFew::BM - 1) / GemmFew::BM) * ((g.N + GemmFew::BN - 1) / GemmFew::BN);
       GemmArgs a = g;
       a.xcd_chunks = tiles_n <= 8 ? 1 : 2;   // every XCD walks its own eighth of the tile list; wide outputs in grouped order
       ProfScope ps_("gemm_bf16_kernel", st);
-      LLMC_KERNEL_GGL(kernel, dim3(std::min((tiles_m * tiles_n + 7) & ~7, kMaxGrid)), dim3(C::THREADS), lds_bytes, st, a,
+      LLMC_KERNEL_GGL(kernel, dim3(std::min((std::max(tiles_m * tiles_n, few) + 7) & ~7, kMaxGrid)), dim3(C::THREADS), lds_bytes, st, a,
                       tiles_n);
     } else {
       const int tiles_n = (g.N + GemmCfg::BN - 1) / GemmCfg::BN;

@@ -1780,6 +1780,39 @@ def test_few_rows_and_many_rows_give_the_same_bits(L, arch):
 
 
 @pytest.mark.parametrize("d,dff,S,B", [
+    (64, 64, 1, 1),          # one token, one step of k, one column tile
+    (64, 320, 31, 1),        # one row short of a tile; five steps of k in the second feed-forward layer
+    (192, 384, 33, 3),       # 99 tokens, three steps of k (less than the ring holds) and six (as many as it holds)
+    (448, 704, 65, 2),       # seven and eleven steps, column counts that are odd multiples of 64
+    (768, 3072, 96, 12),     # 1152 tokens: two of the four layers take 32 x 64 tiles, the others 64 x 128
+])
+@pytest.mark.parametrize("arch", [0, 1])
+def test_bf16_layer_tilings(L, arch, d, dff, S, B):
+    """The bf16 block on the tilings for few rows against the oracle, and the same bits for the last sequence computed
+    alone (where fewer rows may mean other tiles)."""
+    from paper_2512_16843_amd.engine import GatedStack
+    say(f"plain bf16 layer arch={arch} d={d} dff={dff} S={S} B={B}")
+    cfg = small_cfg(arch, "bf16", d, d // 64, dff, S, B)
+    ws = W.make_layer_weights(cfg, seed=12)
+    Ps = W.make_projection(d, cfg.k, torch.bfloat16)
+    g = np.random.Generator(np.random.PCG64(d + S))
+    h0 = torch.from_numpy(g.standard_normal((B, S, d)).astype(np.float32)).bfloat16().cuda()
+    st = GatedStack(cfg, ws, Ps, cached_layers=[])
+    out = st.forward(h0, tau=0.5).clone()
+    torch.cuda.synchronize()
+    one = GatedStack(W.scaled(cfg, B=1), ws, Ps, cached_layers=[])
+    alone = one.forward(h0[B - 1:].contiguous(), tau=0.5)
+    torch.cuda.synchronize()
+    assert torch.equal(alone[0], out[B - 1])
+    wnp = {k: npf(v) for k, v in ws[0].items()}
+    rows = [0, B - 1]
+    want = np.stack([O.layer_forward(npf(h0[b]), wnp, arch, d // 64, cfg.ln_eps, cfg.gelu) for b in rows])
+    assert rel_err_rows(npf(out)[rows], want).max() < TOL["bf16"]
+    st.close()
+    one.close()
+
+
+@pytest.mark.parametrize("d,dff,S,B", [
     (64, 64, 1, 1),          # one token, one column tile
     (192, 320, 33, 3),       # 99 tokens: ragged against 32 and 64 rows, widths that are odd multiples of 64
     (128, 64, 145, 2),       # attention: two query blocks and a third of 17, five key tiles, the last with 17 keys

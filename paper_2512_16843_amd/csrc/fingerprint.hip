@@ -392,15 +392,23 @@ llmc_status_t launch_fingerprint(const void* d_h, const int32_t*, int B, int S, 
 // token means of B whole sequences through the wide pooling kernel: chunk partials first, then one workgroup per
 // sequence adds them in ascending chunk order (the arithmetic of the projection's own chunk sum, so the mean has
 // the bits the fingerprint uses) and writes out[b * ld_out ..] [d]
-__global__ void mean_from_partials_kernel(const float* __restrict__ partial, int n_chunks, int d, float inv_S,
-                                          float* __restrict__ out, int ld_out) {
-  const int b = blockIdx.x;
-  for (int i = threadIdx.x; i < d; i += blockDim.x) {
-    const float* src = partial + (size_t)b * n_chunks * d + i;
-    float s = 0.f;
-    for (int c = 0; c < n_chunks; ++c) s += src[(size_t)c * d];
-    out[(size_t)b * ld_out + i] = s * inv_S;
+// grid (B, ceil(d / 256)): a thread owns one column; sixteen chunk sums are in flight (one at a time, 16 sequences of 16
+// chunks took 12.6 us, now 4.1, where an empty launch is timed at 4.0)
+__global__ __launch_bounds__(256) void mean_from_partials_kernel(const float* __restrict__ partial, int n_chunks, int d,
+                                                                 float inv_S, float* __restrict__ out, int ld_out) {
+  const int b = blockIdx.x, i = blockIdx.y * 256 + threadIdx.x;
+  if (i >= d) return;
+  const float* src = partial + (size_t)b * n_chunks * d + i;
+  float s = 0.f;
+  for (int c = 0; c < n_chunks; c += 16) {
+    float x[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) x[u] = src[(size_t)min(c + u, n_chunks - 1) * d];
+#pragma unroll
+    for (int u = 0; u < 16; ++u)
+      if (c + u < n_chunks) s += x[u];
   }
+  out[(size_t)b * ld_out + i] = s * inv_S;
 }
 
 template <typename T>
@@ -415,7 +423,7 @@ static llmc_status_t pool_means_t(const T* h, int B, int S, int d, float* partia
                     (const int32_t*)nullptr); }
   LLMC_LAUNCH_CHECK("pool_kernel");
   { ProfScope ps_("mean_from_partials_kernel", st);
-    LLMC_KERNEL_GGL(mean_from_partials_kernel, dim3(B), dim3(256), 0, st, partial, n_chunks, d, 1.0f / (float)S, out, ld_out); }
+    LLMC_KERNEL_GGL(mean_from_partials_kernel, dim3(B, (d + 255) / 256), dim3(256), 0, st, partial, n_chunks, d, 1.0f / (float)S, out, ld_out); }
   LLMC_LAUNCH_CHECK("mean_from_partials_kernel");
   return LLMC_OK;
 }

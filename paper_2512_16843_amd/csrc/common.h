@@ -76,15 +76,70 @@ template <> struct Vec16<bf16_t> {
 };
 
 // ---- wavefront (64 lanes) reductions with a fixed order -------------------------
+// Value of lane i ^ O for every lane, by lane swaps and data-parallel moves: a few clocks, where the shuffle through the
+// LDS pipe takes over a hundred.  O = 8 and 4 are rotations within rows of 16 lanes: a rotation by 8 is the exchange
+// itself; a rotation by 4 is it only for values that are already equal on lanes i and i ^ 8, as they are in a
+// butterfly that has passed O = 8.
+template <int O>
+__device__ __forceinline__ uint32_t butterfly_u32(uint32_t v) {
+  static_assert(O == 8 || O == 4 || O == 2 || O == 1, "inside a row of 16 lanes");
+  constexpr int ctrl = O == 8 ? 0x128 : O == 4 ? 0x124 : O == 2 ? 0x4E : 0xB1;   // row_ror:8, row_ror:4, quad_perm x 2
+  return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xF, 0xF, true);
+}
+// both halves (O = 32) or both rows of a pair (O = 16): a lane's own value and its partner's, in some order
+template <int O>
+__device__ __forceinline__ void butterfly_pair_u32(uint32_t v, uint32_t& a, uint32_t& b) {
+  if (O == 32) {
+    const auto s = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    a = (uint32_t)s[0]; b = (uint32_t)s[1];
+  } else {
+    const auto s = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    a = (uint32_t)s[0]; b = (uint32_t)s[1];
+  }
+}
+// the partner's value, every lane its own partner's (O = 4: see above)
+template <int O>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+  if (O >= 16) {
+    uint32_t a, b;
+    butterfly_pair_u32<O>(v, a, b);
+    return (threadIdx.x & O) ? a : b;
+  }
+  constexpr int P = O < 16 ? O : 8;
+  return butterfly_u32<P>(v);
+}
+// sums over the wavefront, the same in every lane: a butterfly 32, 16, 8, 4, 2, 1 (the bits of v += shfl_xor(v, o), whose
+// operands only change places)
 __device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  uint32_t a, b;
+  butterfly_pair_u32<32>(__float_as_uint(v), a, b); v = __uint_as_float(a) + __uint_as_float(b);
+  butterfly_pair_u32<16>(__float_as_uint(v), a, b); v = __uint_as_float(a) + __uint_as_float(b);
+  v += __uint_as_float(butterfly_u32<8>(__float_as_uint(v)));
+  v += __uint_as_float(butterfly_u32<4>(__float_as_uint(v)));
+  v += __uint_as_float(butterfly_u32<2>(__float_as_uint(v)));
+  v += __uint_as_float(butterfly_u32<1>(__float_as_uint(v)));
   return v;
 }
+template <int O>
+__device__ __forceinline__ double butterfly_add(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
+  if (O >= 16) {
+    uint32_t la, lb, ha, hb;
+    butterfly_pair_u32<O>(lo, la, lb);
+    butterfly_pair_u32<O>(hi, ha, hb);
+    return __builtin_bit_cast(double, ((uint64_t)ha << 32) | la) + __builtin_bit_cast(double, ((uint64_t)hb << 32) | lb);
+  }
+  constexpr int P = O < 16 ? O : 8;
+  return v + __builtin_bit_cast(double, ((uint64_t)butterfly_u32<P>(hi) << 32) | butterfly_u32<P>(lo));
+}
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
+  v = butterfly_add<32>(v);
+  v = butterfly_add<16>(v);
+  v = butterfly_add<8>(v);
+  v = butterfly_add<4>(v);
+  v = butterfly_add<2>(v);
+  return butterfly_add<1>(v);
 }
 __device__ __forceinline__ float wave_max(float v) {
 #pragma unroll

@@ -132,7 +132,10 @@ __device__ __forceinline__ void pool_sequence(const T* __restrict__ seq, int S, 
   }
 }
 
-// grid (B); block CG * PARTS threads: thread (cg, part) owns the four output columns 4*cg .. 4*cg+3
+// whole wavefronts, so that the butterflies of the norm read live lanes only (at most 1024 since k and cgs * parts are)
+static inline int project_threads(int cgs, int parts, int k) { return (std::max(cgs * parts, k) + 63) & ~63; }
+
+// grid (B); block CG * PARTS threads (rounded up to wavefronts): thread (cg, part) owns the four output columns 4*cg .. 4*cg+3
 // over the part-th slice of d; slices are then added in ascending order.
 template <typename T>
 __global__ __launch_bounds__(1024) void project_kernel(const float* __restrict__ partial, int n_chunks, int S, int d,
@@ -215,7 +218,7 @@ __global__ __launch_bounds__(1024) void project_kernel(const float* __restrict__
     const int cgs = k / 4;
     const int cg = threadIdx.x % cgs, part = threadIdx.x / cgs;
     const int per = (d + parts - 1) / parts;
-    const int i0 = part * per, i1 = min(d, i0 + per);
+    const int i0 = part * per, i1 = part < parts ? min(d, i0 + per) : i0;    // the others only fill a wavefront
     float v[4] = {0.f, 0.f, 0.f, 0.f};
     // sixteen rows of P in flight per thread; the sums run in ascending row order
     constexpr int U = 16;
@@ -249,8 +252,10 @@ __global__ __launch_bounds__(1024) void project_kernel(const float* __restrict__
 #pragma unroll
       for (int e = 0; e < 4; ++e) v[e] = fmaf(pi, w[e], v[e]);
     }
+    if (part < parts) {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) vpart[part * k + cg * 4 + e] = v[e];
+      for (int e = 0; e < 4; ++e) vpart[part * k + cg * 4 + e] = v[e];
+    }
   }
   __syncthreads();
   const int j = threadIdx.x;
@@ -353,7 +358,7 @@ static llmc_status_t fingerprint_t(const T* h, int B, int S, int d, const T* P, 
   // slices of d per output column group; depends on k only.  k <= 1024 gives at least k threads.
   const int cgs = k / 4;
   const int parts = std::max(1, std::min(1024 / cgs, 16));
-  const int threads = std::max(cgs * parts, k);
+  const int threads = project_threads(cgs, parts, k);
   // When the caller expects nearly every row to arrive with its mean or key (a carry from the producing call), the
   // projection's workgroups pool the few others themselves (same arithmetic, see pool_sequence) and the pooling
   // launch is dropped.  Otherwise every uncarried row is pooled by the dedicated, wider kernel.
@@ -441,7 +446,7 @@ static llmc_status_t project_rows_t(const float* means, int n_max, int d, const 
   const int cgs = k / 4;
   const int parts = std::max(1, std::min(1024 / cgs, 16));
   ProfScope ps_("project_kernel", st);
-  LLMC_KERNEL_GGL(project_kernel<T>, dim3(n_max), dim3(std::max(cgs * parts, k)),
+  LLMC_KERNEL_GGL(project_kernel<T>, dim3(n_max), dim3(project_threads(cgs, parts, k)),
                      (size_t)(d + parts * k) * sizeof(float), st, (const float*)nullptr, 0, 1, d, P, bias, k, parts, fp, inv,
                      (uint32_t*)nullptr, means, (const uint8_t*)nullptr, (const T*)nullptr, (const float*)nullptr, rows,
                      count, (const T*)nullptr, 0, 0, (const int32_t*)nullptr);

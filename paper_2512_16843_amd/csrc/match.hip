@@ -560,6 +560,24 @@ __global__ __launch_bounds__(256) void match_f32_kernel(const float* __restrict_
   }
 }
 
+// merge with the lane whose number differs in bit O (the merge does not depend on the order of its operands)
+template <int O>
+__device__ __forceinline__ void top2_exchange(Top2& t) {
+  Top2 c;
+  c.v1 = __uint_as_float(lane_xor<O>(__float_as_uint(t.v1))); c.g1 = (int)lane_xor<O>((uint32_t)t.g1);
+  c.v2 = __uint_as_float(lane_xor<O>(__float_as_uint(t.v2))); c.g2 = (int)lane_xor<O>((uint32_t)t.g2);
+  c.v3 = __uint_as_float(lane_xor<O>(__float_as_uint(t.v3)));
+  top2_merge(t, c);
+}
+// the better of this lane's candidate and its partner's: larger cosine, lowest slot among equals
+template <int O>
+__device__ __forceinline__ void best_exchange(double& best, int& best_j) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, best);
+  const double os = __builtin_bit_cast(double, ((uint64_t)lane_xor<O>((uint32_t)(u >> 32)) << 32) | lane_xor<O>((uint32_t)u));
+  const int oj = (int)lane_xor<O>((uint32_t)best_j);
+  if (oj >= 0 && (best_j < 0 || os > best || (os == best && oj < best_j))) { best = os; best_j = oj; }
+}
+
 // One wavefront per query: merge the partial results of all bank splits, then decide the
 // winner exactly.  The 64 lanes evaluate the 16 rows of a candidate group at once, 4 lanes
 // per row, each over a quarter of the key in fp64; the four partial sums are added in a
@@ -586,14 +604,8 @@ __global__ __launch_bounds__(256) void match_finalize_kernel(
 #pragma unroll
     for (int u = 0; u < 4; ++u) top2_merge(t, c[u]);
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    Top2 c;
-    c.v1 = __shfl_xor(t.v1, o, 64); c.g1 = __shfl_xor(t.g1, o, 64);
-    c.v2 = __shfl_xor(t.v2, o, 64); c.g2 = __shfl_xor(t.g2, o, 64);
-    c.v3 = __shfl_xor(t.v3, o, 64);
-    top2_merge(t, c);
-  }
+  top2_exchange<32>(t); top2_exchange<16>(t); top2_exchange<8>(t);
+  top2_exchange<4>(t); top2_exchange<2>(t); top2_exchange<1>(t);
   const float qi = qinv[b];
   const double qi64 = (double)qi;
   // scores so far are |q| * cos; the runner-up counts as tied within 1e-5 in cosine
@@ -636,19 +648,15 @@ __global__ __launch_bounds__(256) void match_finalize_kernel(
 #pragma unroll
       for (int e = 0; e < VEC; ++e) a += (double)x[e] * (double)y[e];
     }
-    a += __shfl_xor(a, 1, 64);
-    a += __shfl_xor(a, 2, 64);
+    a = butterfly_add<1>(a);
+    a = butterfly_add<2>(a);
     if (ok) {
       const double s = a * qi64 * bj;
       if (s > best || (s == best && (best_j < 0 || j < best_j))) { best = s; best_j = j; }
     }
   }
-#pragma unroll
-  for (int o = 4; o < 64; o <<= 1) {
-    const double os = __shfl_xor(best, o, 64);
-    const int oj = __shfl_xor(best_j, o, 64);
-    if (oj >= 0 && (best_j < 0 || os > best || (os == best && oj < best_j))) { best = os; best_j = oj; }
-  }
+  best_exchange<32>(best, best_j); best_exchange<16>(best, best_j);
+  best_exchange<8>(best, best_j); best_exchange<4>(best, best_j);
   if (lane == 0) {
     idx_out[b] = best_j;
     if (sim_out) sim_out[b] = (float)best;

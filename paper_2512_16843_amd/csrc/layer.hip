@@ -45,7 +45,11 @@ static llmc_status_t launch_gemm(const GemmArgs& g, int dtype, hipStream_t st) {
       const int tiles_m = (g.max_seqs * g.S + CS::BM - 1) / CS::BM;
       const int few = ((g.max_seqs * g.S + GemmFew::BM - 1) / GemmFew::BM) * ((g.N + GemmFew::BN - 1) / GemmFew::BN);
       GemmArgs a = g;
-      a.xcd_chunks = tiles_n <= 8 ? 1 : 2;   // every XCD walks its own eighth of the tile list; wide outputs in grouped order
+      // Every XCD walks its own eighth of the tile list, wide outputs in grouped order; where the column tiles divide by
+      // eight, plain striding gives each XCD its own eighth of the COLUMNS instead, so the L2 keeps its weights and only
+      // the rows stream (4096 rows, K = 1024: 3072 columns 38.8 -> 33.2 us, 4096 columns 49.6 -> 45.8; 24576 rows of
+      // K = 768 the same either way; 18 column tiles strided 120 us against 114).
+      a.xcd_chunks = tiles_n <= 8 ? 1 : tiles_n % 8 == 0 ? 0 : 2;
       ProfScope ps_("gemm_bf16_kernel", st);
       LLMC_KERNEL_GGL(kernel, dim3(std::min((std::max(tiles_m * tiles_n, few) + 7) & ~7, kMaxGrid)), dim3(C::THREADS), lds_bytes, st, a,
                       tiles_n);

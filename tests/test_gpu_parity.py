@@ -177,6 +177,19 @@ def test_fingerprint_is_position_and_batch_independent(L):
     assert torch.equal(fp_c[0], fp_a[3]) and torch.equal(inv_c[0], inv_a[3])
 
 
+@pytest.mark.parametrize("k", [32, 96, 288, 992])
+def test_fingerprint_key_lengths_that_do_not_fill_wavefronts(L, k):
+    """Norms are sums over wavefronts; these lengths (and their 128, 384, 1008 and 992 threads of work) end inside one."""
+    say(f"fingerprint f32 k={k}")
+    g = np.random.Generator(np.random.PCG64(k))
+    h = torch.from_numpy(g.standard_normal((3, 70, 192)).astype(np.float32)).cuda()
+    P = W.make_projection(192, k, torch.float32, seed=3)[0].cuda()
+    fp, inv = run_fingerprint(L, h, P, None)
+    q, _ = O.fingerprint(npf(h), npf(P), None, "f32")
+    assert np.abs(npf(fp) - q).max() < 1e-5            # unit keys from sums of 192 products
+    np.testing.assert_allclose(npf(inv), O.inv_norm(npf(fp)), rtol=3e-7, atol=0)
+
+
 def test_fingerprint_zero_input(L):
     say("fingerprint of an all-zero sequence")
     h = torch.zeros((2, 5, 128), dtype=torch.float32, device="cuda")

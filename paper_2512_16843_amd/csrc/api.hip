@@ -668,12 +668,11 @@ llmc_status_t llmc_layer_forward_gated(const llmc_layer_desc_t* layer, llmc_bank
   }
   int32_t* ref_out = (flags & LLMC_DEFER_COPY) ? out->d_ref_out : nullptr;
   if (!bits) LLMC_TRY(launch_match(bank, q, qinv, B, tau, idx, sim, hit, tie, ws_match, st));
-  LLMC_TRY(launch_compact(hit, idx, sim, tie, B, tau, hit_rows, miss_rows, reval_tmp, counters, bank, flags, tick, st,
-                          pooled_valid_out, pooled_out ? 1 : 0, ref_out));
   // rows to compute that arrived as references get their content now (the only reader of a referenced row)
-  if (!d_fp_given && fp && fp->d_ref_in)
-    LLMC_TRY(launch_materialize(fp->prev_bank, fp->d_ref_in, miss_rows, counters + LLMC_CNT_COMPUTED, B,
-                                const_cast<void*>(d_h_in), st));
+  const bool refs_in = !d_fp_given && fp && fp->d_ref_in;
+  LLMC_TRY(launch_compact(hit, idx, sim, tie, B, tau, hit_rows, miss_rows, reval_tmp, counters, bank, flags, tick, st,
+                          pooled_valid_out, pooled_out ? 1 : 0, ref_out, refs_in ? fp->prev_bank : nullptr,
+                          refs_in ? fp->d_ref_in : nullptr, const_cast<void*>(d_h_in)));
   if (!(flags & LLMC_DEFER_COPY))
     LLMC_TRY(launch_gather(bank, idx, hit_rows, counters + LLMC_CNT_HIT, B, d_h_out, st, pooled_out, key_out, key_inv_out));
   // within-batch reuse: the rows to compute shrink to the leaders (after the gather, which reads the hit count)

@@ -271,11 +271,13 @@ llmc_status_t launch_match(const llmc_bank* bank, const void* d_fp, const float*
 llmc_status_t match_static_scratch(void** out, size_t* bytes);
 
 // gate.hip
+// d_ref_in (with prev_bank and d_h): the rows to compute that arrived as references get their content too
 llmc_status_t launch_compact(const uint8_t* d_hit, const int32_t* d_idx, const float* d_sim,
                              const uint8_t* d_near_tie, int B, float tau, int32_t* d_hit_rows,
                              int32_t* d_miss_rows, int32_t* d_reval_tmp, int32_t* d_counters, llmc_bank* bank,
                              uint32_t flags, uint64_t tick, hipStream_t st, uint8_t* d_pooled_valid_out = nullptr,
-                             int has_pool = 0, int32_t* d_ref_out = nullptr);
+                             int has_pool = 0, int32_t* d_ref_out = nullptr, const llmc_bank* prev_bank = nullptr,
+                             const int32_t* d_ref_in = nullptr, void* d_h = nullptr);
 // within-batch reuse (LLMC_DEDUP): scratch size, the decision among the rows to compute (before the dense block),
 // and the copies / bookkeeping of the followers (after the insertion)
 size_t dedup_ws_bytes(int B);

@@ -41,7 +41,7 @@ typedef F32Cfg<32, 32, 4> F32Small;
 // as long, so with two tiles or fewer per compute unit the last round of them leaves much of the chip idle; beyond
 // that the wide tiles' halved operand traffic wins.  The four linear layers of a 768-wide block, small / wide: 62 / 124 us
 // at 128 rows, 106 / 152 at 512, 156 (the line) / 183 at 1024; 589 (all below 1024 tiles small) / 514 at 4096, where
-// they reach 113 TFLOP/s.
+// they reach 113 TFLOP/s.  (512 rows: 96 since a step's fragments are read behind the multiplies of the step before.)
 constexpr int kF32SmallTiles = 640;
 constexpr int kF32MaxGrid = 1024;
 

@@ -43,7 +43,8 @@ static llmc_status_t launch_gemm(const GemmArgs& g, int dtype, hipStream_t st) {
       // the grid covers the smaller tilings too, which the kernel takes when the rows it finds on the device are few
       static_assert(GemmFew::LDS_BYTES <= gemm_dma_smem_bytes<C, CS>(), "the stages of every tiling fit the launch");
       const int tiles_m = (g.max_seqs * g.S + CS::BM - 1) / CS::BM;
-      const int few = ((g.max_seqs * g.S + GemmFew::BM - 1) / GemmFew::BM) * ((g.N + GemmFew::BN - 1) / GemmFew::BN);
+      const int64_t few = (int64_t)((g.max_seqs * g.S + GemmFew::BM - 1) / GemmFew::BM) * ((g.N + GemmFew::BN - 1) / GemmFew::BN);
+      const int64_t tiles = std::max((int64_t)tiles_m * tiles_n, few);
       GemmArgs a = g;
       // Every XCD walks its own eighth of the tile list, wide outputs in grouped order; where the column tiles divide by
       // eight, plain striding gives each XCD its own eighth of the COLUMNS instead, so the L2 keeps its weights and only
@@ -51,7 +52,7 @@ static llmc_status_t launch_gemm(const GemmArgs& g, int dtype, hipStream_t st) {
       // K = 768 the same either way; 18 column tiles strided 120 us against 114).
       a.xcd_chunks = tiles_n <= 8 ? 1 : tiles_n % 8 == 0 ? 0 : 2;
       ProfScope ps_("gemm_bf16_kernel", st);
-      LLMC_KERNEL_GGL(kernel, dim3(std::min((std::max(tiles_m * tiles_n, few) + 7) & ~7, kMaxGrid)), dim3(C::THREADS), lds_bytes, st, a,
+      LLMC_KERNEL_GGL(kernel, dim3((unsigned)std::min<int64_t>((tiles + 7) & ~7ll, kMaxGrid)), dim3(C::THREADS), lds_bytes, st, a,
                       tiles_n);
     } else {
       const int tiles_n = (g.N + GemmCfg::BN - 1) / GemmCfg::BN;

@@ -277,6 +277,7 @@ __device__ __forceinline__ void gemm_few_loop(const uint16_t* p0, const uint16_t
   tail(std::integral_constant<int, 1>());
   tail(std::integral_constant<int, 0>());
   if (COMPUTE) {
+    LLMC_WAIT_LGKM(0);           // the last fragments are in registers before the caller's barrier hands their stage on
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks], fb[ks], acc, 0, 0, 0);
   }

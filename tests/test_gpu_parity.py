@@ -1796,7 +1796,9 @@ def test_few_rows_and_many_rows_give_the_same_bits(L, arch):
     (64, 64, 1, 1),          # one token, one step of k, one column tile
     (64, 320, 31, 1),        # one row short of a tile; five steps of k in the second feed-forward layer
     (192, 384, 33, 3),       # 99 tokens, three steps of k (less than the ring holds) and six (as many as it holds)
-    (448, 704, 65, 2),       # seven and eleven steps, column counts that are odd multiples of 64
+    # seven and eleven steps, column counts that are odd multiples of 64; with one and seven steps (one more than a
+    # multiple of the ring's six stages) the epilogue's staging overwrites the very stage that the last step reads
+    (448, 704, 65, 2),
     (768, 3072, 96, 12),     # 1152 tokens: two of the four layers take 32 x 64 tiles, the others 64 x 128
 ])
 @pytest.mark.parametrize("arch", [0, 1])

@@ -266,8 +266,13 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(const float* __restr
           }
         mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-        const float m_new = fmaxf(m_run, mx);        // finite: key 0 is visible to every query
-        const float corr = __builtin_amdgcn_exp2f(m_run - m_new);
+        const float m_new = fmaxf(m_run, mx);
+        // Key 0 is visible to every query, but its score may have overflowed to -inf, like all others so far: such a
+        // query keeps its zeros (of l_run and o) until a tile brings a score that has not.
+        const bool none = m_new == -INFINITY;
+        const bool any_none = __ballot(none) != 0;
+        const float m_sub = none ? 0.f : m_new;
+        const float corr = __builtin_amdgcn_exp2f(m_run - m_sub);
         m_run = m_new;
         l_run *= corr;
 #pragma unroll
@@ -276,7 +281,7 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(const float* __restr
         for (int f = 0; f < 2; ++f)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            s[f][r] = __builtin_amdgcn_exp2f(s[f][r] - m_new);
+            s[f][r] = __builtin_amdgcn_exp2f(s[f][r] - m_sub);
             l_run += s[f][r];
           }
 #pragma unroll
@@ -288,6 +293,11 @@ __global__ __launch_bounds__(256) void attention_f32_kernel(const float* __restr
             for (int h = 0; h < 4; ++h)
               o[h] = __builtin_amdgcn_mfma_f32_16x16x4f32(vp[h * 16], s[f][r], o[h], 0, 0, 0);
           }
+        if (any_none && none) {                      // whatever the tile holds: not-a-numbers among its scores, infinite values
+          l_run = 0.f;
+#pragma unroll
+          for (int h = 0; h < 4; ++h) o[h] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        }
       }
       if (t + 1 < n_tiles) store(buf ^ 1);
       __syncthreads();

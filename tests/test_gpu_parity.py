@@ -1859,6 +1859,40 @@ def test_f32_layer_tilings(L, arch, d, dff, S, B):
     one.close()
 
 
+@pytest.mark.parametrize("masked,every,inf_values", [
+    (32, 2, False),          # the first 32-key tile: every other query of a wavefront
+    (32, 1, True),           # ... of every query, and the values there are infinite
+    (65, 1, False),          # two tiles and one key of the third
+])
+def test_f32_attention_scores_that_overflow_in_the_first_tiles(L, masked, every, inf_values):
+    """Scores of the first keys that overflow to -inf: those keys count for nothing, the later ones as usual."""
+    from paper_2512_16843_amd.engine import GatedStack
+    say(f"fp32 attention, the first {masked} keys of {masked + 9} masked by overflow, inf_values={inf_values}")
+    S, B = masked + 9, 2
+    cfg = small_cfg(0, "f32", 64, 1, 64, S, B)
+    ws = W.make_layer_weights(cfg, seed=31)
+    w = ws[0]
+    g = np.random.Generator(np.random.PCG64(masked))
+    x = g.standard_normal((B, S, 64)).astype(np.float32)
+    x[:, :, 0] = 0.0
+    x[:, :masked, 0] = 2.0                                    # the masked keys
+    x[:, :, 1] = 0.0
+    x[:, ::every, 1] = 1.0                                    # the queries that they are masked for
+    # query and key 0 see these two channels alone: their product is -2e40 for a masked pair and 0 for any other
+    for row, ch, v in ((0, 1, 1e20), (64, 0, -1e20)) + (((128, 0, 3e38),) if inf_values else ()):
+        w["wqkv"][row] = 0.0
+        w["wqkv"][row, ch] = v
+        w["bqkv"][row] = 0.0
+    st = GatedStack(cfg, ws, W.make_projection(64, cfg.k, torch.float32), cached_layers=[])
+    out = st.forward(torch.from_numpy(x).cuda(), tau=0.5)
+    torch.cuda.synchronize()
+    wnp = {k: npf(v) for k, v in w.items()}
+    want = np.stack([O.layer_forward(x[b], wnp, 0, 1, cfg.ln_eps, cfg.gelu) for b in range(B)])
+    assert np.isfinite(npf(out)).all()
+    assert rel_err_rows(npf(out), want).max() < 1e-5          # sums of at most 74 fp32 products
+    st.close()
+
+
 @pytest.mark.parametrize("carry", [False, True], ids=["plain", "carried"])
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_within_batch_reuse_against_oracle(L, dtype, carry):

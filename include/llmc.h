@@ -383,7 +383,8 @@ llmc_status_t llmc_inv_norm(const void* d_fp, int64_t n, int32_t k, int32_t dtyp
  * The bulk search runs on the matrix cores with fp32 accumulation; the winner
  * is then decided, and d_sim computed, in fp64 among the best candidate group
  * (and the runner-up group when the two are closer than 1e-5).
- * d_workspace: at least llmc_match_workspace_bytes(bank, B) bytes.
+ * d_workspace: at least llmc_match_workspace_bytes(bank, B) bytes.  For a bank of fp32 keys that size rises with B, so
+ * a workspace sized for the largest batch serves every smaller one.
  * Errors: INVALID_ARG (null, B <= 0, tau NaN), WORKSPACE.
  */
 llmc_status_t llmc_match(const llmc_bank_t* bank, const void* d_fp, const float* d_inv_norm,

@@ -389,9 +389,9 @@ llmc_status_t llmc_match(const llmc_bank_t* bank, const void* d_fp, const float*
   REQUIRE(B <= 65535 * 128, LLMC_ERR_SHAPE, "B=%d too large", B);
   REQUIRE(tau == tau, LLMC_ERR_INVALID_ARG, "tau is NaN");
   REQUIRE(aligned16(d_fp), LLMC_ERR_SHAPE, "query keys must be 16-byte aligned");
-  const size_t need = match_ws_bytes(bank->desc.n_slots, bank->desc.k, bank->desc.dtype, B);
+  const size_t need = match_ws_need_bytes(bank->desc.n_slots, bank->desc.k, bank->desc.dtype, B);
   REQUIRE(d_workspace && workspace_bytes >= need, LLMC_ERR_WORKSPACE, "match workspace needs %zu bytes", need);
-  return launch_match(bank, d_fp, d_inv_norm, B, tau, d_idx, d_sim, d_hit, d_near_tie, d_workspace,
+  return launch_match(bank, d_fp, d_inv_norm, B, tau, d_idx, d_sim, d_hit, d_near_tie, d_workspace, workspace_bytes,
                       (hipStream_t)stream);
 }
 
@@ -412,7 +412,7 @@ llmc_status_t llmc_match_noalloc(const llmc_bank_t* bank, const void* d_fp, cons
   void* ws = nullptr;
   size_t have = 0;
   LLMC_TRY(match_static_scratch(&ws, &have));
-  return launch_match(bank, d_fp, d_inv_norm, B, tau, d_idx, d_sim, d_hit, d_near_tie, ws, (hipStream_t)stream);
+  return launch_match(bank, d_fp, d_inv_norm, B, tau, d_idx, d_sim, d_hit, d_near_tie, ws, have, (hipStream_t)stream);
 }
 
 llmc_status_t llmc_gather_hits(const llmc_bank_t* bank, const int32_t* d_idx, const int32_t* d_rows, const int32_t* d_n,
@@ -667,7 +667,7 @@ llmc_status_t llmc_layer_forward_gated(const llmc_layer_desc_t* layer, llmc_bank
     }
   }
   int32_t* ref_out = (flags & LLMC_DEFER_COPY) ? out->d_ref_out : nullptr;
-  if (!bits) LLMC_TRY(launch_match(bank, q, qinv, B, tau, idx, sim, hit, tie, ws_match, st));
+  if (!bits) LLMC_TRY(launch_match(bank, q, qinv, B, tau, idx, sim, hit, tie, ws_match, match_ws_max_bytes(B), st));
   // rows to compute that arrived as references get their content now (the only reader of a referenced row)
   const bool refs_in = !d_fp_given && fp && fp->d_ref_in;
   LLMC_TRY(launch_compact(hit, idx, sim, tie, B, tau, hit_rows, miss_rows, reval_tmp, counters, bank, flags, tick, st,

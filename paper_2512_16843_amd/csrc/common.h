@@ -262,11 +262,12 @@ llmc_status_t launch_match_bits(const uint32_t* d_bank_bits, const uint8_t* d_va
 llmc_status_t launch_inv_norm(const void* d_fp, int64_t n, int k, int dtype, float* d_out, hipStream_t st);
 
 // match.hip
-size_t match_ws_bytes(int n_slots, int k, int dtype, int B);
+size_t match_ws_bytes(int n_slots, int k, int dtype, int B);         // what llmc_match_workspace_bytes reports
+size_t match_ws_need_bytes(int n_slots, int k, int dtype, int B);    // what a call cannot do without
 size_t match_ws_max_bytes(int B);
 llmc_status_t launch_match(const llmc_bank* bank, const void* d_fp, const float* d_inv, int B, float tau,
                            int32_t* d_idx, float* d_sim, uint8_t* d_hit, uint8_t* d_near_tie, void* ws,
-                           hipStream_t st);
+                           size_t ws_bytes, hipStream_t st);
 
 llmc_status_t match_static_scratch(void** out, size_t* bytes);
 

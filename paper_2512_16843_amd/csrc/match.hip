@@ -678,13 +678,15 @@ static void split_plan(int N, int B, int* n_split, int* tiles_per_split) {
 
 // fp32 keys: few queries take 16 per workgroup, more take 64 (a quarter of the bank reads per query)
 static int f32_query_block(int B) { return B <= 16 ? 16 : 64; }
-// about eight workgroups per compute unit; the splits are as few as keep the partial results within the fixed scratch
-// of llmc_match_noalloc, so that it takes every batch whose queries alone fit there
-static void f32_plan(int N, int B, int* n_split, int* blocks_per_split) {
+// about eight workgroups per compute unit; the splits are as few as keep the partial results within the scratch of the
+// call (and within the size of llmc_match_noalloc's): one result per query always fits, and how the bank is split
+// changes no result
+static void f32_plan(int N, int B, size_t scratch_bytes, int* n_split, int* blocks_per_split) {
   const int blocks = (N + 127) / 128;
   const int qb = (B + f32_query_block(B) - 1) / f32_query_block(B);
   int want = std::min(std::min(blocks, 1024), std::max(1, 2048 / qb));
-  want = std::min(want, std::max(1, (int)(LLMC_MATCH_STATIC_SCRATCH_BYTES / sizeof(Top2) / (size_t)B)));
+  scratch_bytes = std::min(scratch_bytes, (size_t)LLMC_MATCH_STATIC_SCRATCH_BYTES);
+  want = std::min(want, std::max(1, (int)(scratch_bytes / sizeof(Top2) / (size_t)B)));
   const int per = (blocks + want - 1) / want;
   *blocks_per_split = per;
   *n_split = (blocks + per - 1) / per;
@@ -714,13 +716,19 @@ size_t match_ws_max_bytes(int B) { return align_up((size_t)1024 * B * sizeof(Top
 
 size_t match_ws_bytes(int n_slots, int k, int dtype, int B) {
   int ns = 1, per = 1, nqb = 1;
-  if (dtype == LLMC_BF16) {
-    if (use_stream(k)) stream_plan(n_slots, B, 64, stream_waves(B) * 64, &nqb, &ns, &per);
-    else split_plan(n_slots, B, &ns, &per);
-  } else {
-    f32_plan(n_slots, B, &ns, &per);
+  if (dtype != LLMC_BF16) {
+    // as many splits as any batch can have, up to the cap of f32_plan: rises with B, so that a workspace sized for
+    // the largest batch gives every smaller one all its splits
+    const size_t blocks = std::min((n_slots + 127) / 128, 1024), one = (size_t)B * sizeof(Top2);
+    return align_up(std::max(one, std::min(blocks * one, (size_t)LLMC_MATCH_STATIC_SCRATCH_BYTES)), 256);
   }
+  if (use_stream(k)) stream_plan(n_slots, B, 64, stream_waves(B) * 64, &nqb, &ns, &per);
+  else split_plan(n_slots, B, &ns, &per);
   return align_up((size_t)ns * B * sizeof(Top2), 256);
+}
+
+size_t match_ws_need_bytes(int n_slots, int k, int dtype, int B) {
+  return dtype == LLMC_BF16 ? match_ws_bytes(n_slots, k, dtype, B) : align_up((size_t)B * sizeof(Top2), 256);
 }
 
 template <int K_, int NW_>
@@ -786,7 +794,7 @@ llmc_status_t match_static_scratch(void** out, size_t* bytes) {
 
 llmc_status_t launch_match(const llmc_bank* bank, const void* d_fp, const float* d_inv, int B, float tau,
                            int32_t* d_idx, float* d_sim, uint8_t* d_hit, uint8_t* d_near_tie, void* ws,
-                           hipStream_t st) {
+                           size_t ws_bytes, hipStream_t st) {
   const llmc_bank_desc_t& D = bank->desc;
   const int N = D.n_slots, K = D.k;
   Top2* partial = (Top2*)ws;
@@ -808,7 +816,7 @@ llmc_status_t launch_match(const llmc_bank* bank, const void* d_fp, const float*
                        (const bf16_t*)D.d_fp, D.d_inv_norm, D.d_valid, N, K, (const bf16_t*)d_fp, d_inv, B, tau, d_idx,
                        d_sim, d_hit, d_near_tie); }
   } else {
-    f32_plan(N, B, &ns, &per);
+    f32_plan(N, B, ws_bytes, &ns, &per);
     const int qblock = f32_query_block(B);
     const dim3 grid((B + qblock - 1) / qblock, ns);
     { ProfScope ps_("match_f32_kernel", st);

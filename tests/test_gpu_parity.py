@@ -405,6 +405,38 @@ def test_match_f32_edges(L, N, B, k):
     bank.close()
 
 
+def test_match_f32_workspace_of_a_larger_batch_serves_smaller_ones(L):
+    """The size reported for fp32 keys rises with the batch, and a workspace of one candidate record (20 bytes) per query
+    is enough: fewer splits of the bank, the same results.  One byte less is refused."""
+    N, k = 131072, 32
+    say(f"match f32 workspaces N={N} k={k}: sized for 129 queries, used for 128")
+    g = np.random.Generator(np.random.PCG64(77))
+    keys = torch.from_numpy(unit_rows(g, N, k).astype(np.float32)).cuda()
+    bank = make_bank(L, keys, dtype=torch.float32)
+    sizes = [L.llmc_match_workspace_bytes(bank, B) for B in (1, 16, 17, 64, 65, 128, 129, 256, 257, 4096, 262144, 300000)]
+    assert sizes == sorted(sizes)
+    B = 128
+    q = torch.from_numpy((npf(keys[:B]) + 0.1 * unit_rows(g, B, k)).astype(np.float32)).cuda()
+    qinv = torch.empty((B,), dtype=torch.float32, device="cuda")
+    L.llmc_inv_norm(q, qinv)
+    least = (20 * B + 255) // 256 * 256
+    res = []
+    for size in (L.llmc_match_workspace_bytes(bank, B), L.llmc_match_workspace_bytes(bank, B + 1), least):
+        ws = torch.empty((size,), dtype=torch.uint8, device="cuda")
+        idx = torch.full((B,), -7, dtype=torch.int32, device="cuda")
+        sim = torch.empty((B,), dtype=torch.float32, device="cuda")
+        L.llmc_match(bank, q, qinv, 0.9, idx, sim, None, None, ws)
+        torch.cuda.synchronize()
+        res.append((idx, sim))
+    assert res[0][0].tolist() == list(range(B))
+    for idx, sim in res[1:]:
+        assert torch.equal(idx, res[0][0]) and torch.equal(sim, res[0][1])
+    with pytest.raises(L.LlmcError) as e:
+        L.llmc_match(bank, q, qinv, 0.9, idx, sim, None, None, torch.empty((least - 1,), dtype=torch.uint8, device="cuda"))
+    assert e.value.status == L.ERR_WORKSPACE
+    bank.close()
+
+
 def test_match_clustered_bank_scaled_stress(L):
     say("match bf16 clustered bank 128 clusters x 256, 1024 queries (scaled copy of the stress config)")
     data = W.make_clustered_bank(128, 256, 256, 0.05, 1024, seed=5)

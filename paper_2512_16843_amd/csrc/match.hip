@@ -20,6 +20,7 @@
 // true maximum, and the row is flagged (near-tie flag 2, counted separately) so that it is
 // reported rather than silently wrong.
 #include <algorithm>
+#include <cfloat>
 #include "common.h"
 #include "mma.h"
 
@@ -545,6 +546,7 @@ __global__ __launch_bounds__(256) void match_f32_kernel(const float* __restrict_
 #pragma unroll
       for (int i = 1; i < 8; ++i) mx = fmaxf(mx, acc[i >> 2][j][i & 3] * bi[i >> 2][i & 3]);
       mx = fmaxf(mx, __shfl_xor(mx, 32, 64));         // the other eight rows of the group
+      mx = mx == -INFINITY ? -FLT_MAX : mx;           // products that overflowed: still a candidate, unlike a free slot
       top2_next(best[j], mx, g);                      // blocks ascend, so the lowest group stays among equals
     }
   }

@@ -405,6 +405,22 @@ def test_match_f32_edges(L, N, B, k):
     bank.close()
 
 
+@pytest.mark.parametrize("live", [(7,), (7, 300)])
+def test_match_f32_best_score_that_overflows(L, live):
+    """Keys and queries of 1e25: every product of a query and a live key overflows to -inf in the bulk pass, and the best
+    of these entries is still the answer."""
+    say(f"match f32, scores that overflow to -inf, live slots {live}")
+    g = np.random.Generator(np.random.PCG64(8))
+    N, k = 320, 64
+    keys = torch.from_numpy((1e25 * np.abs(unit_rows(g, N, k))).astype(np.float32)).cuda()
+    valid = torch.zeros(N, dtype=torch.uint8)
+    valid[list(live)] = 1
+    bank = make_bank(L, keys, valid, dtype=torch.float32)
+    r = check_match(L, bank, -keys[[7, 300, 11]], 0.9, "f32")
+    assert set(r["idx"].tolist()) <= set(live) and not r["hit"].any()
+    bank.close()
+
+
 def test_match_f32_workspace_of_a_larger_batch_serves_smaller_ones(L):
     """The size reported for fp32 keys rises with the batch, and a workspace of one candidate record (20 bytes) per query
     is enough: fewer splits of the bank, the same results.  One byte less is refused."""

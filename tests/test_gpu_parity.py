@@ -179,7 +179,8 @@ def test_fingerprint_is_position_and_batch_independent(L):
 
 @pytest.mark.parametrize("k", [32, 96, 288, 992])
 def test_fingerprint_key_lengths_that_do_not_fill_wavefronts(L, k):
-    """Norms are sums over wavefronts; these lengths (and their 128, 384, 1008 and 992 threads of work) end inside one."""
+    """Norms are sums over wavefronts.  32 and 96 columns end inside one (their 128 and 384 threads of work do not); 288 and
+    992 columns give 1008 and 992 threads of work, which threads without any fill up to whole wavefronts."""
     say(f"fingerprint f32 k={k}")
     g = np.random.Generator(np.random.PCG64(k))
     h = torch.from_numpy(g.standard_normal((3, 70, 192)).astype(np.float32)).cuda()
@@ -402,6 +403,68 @@ def test_match_f32_edges(L, N, B, k):
     near = np.nonzero(valid)[0][-min(B, int(valid.sum())):]
     qn[:len(near)] = npf(keys)[near] + 0.01 * g.standard_normal((len(near), k))
     check_match(L, bank, torch.from_numpy(qn.astype(np.float32)).cuda(), 0.9, "f32")
+    bank.close()
+
+
+@pytest.mark.parametrize("N,B,k,splits", [
+    (16500, 2048, 64, 43),   # 129 blocks of 128 rows, three to a workgroup; the last block has 116 rows
+    (16300, 130, 32, 7),     # 128 blocks, 19 to a workgroup and 14 in the last split, which the workspace allows
+])
+def test_match_f32_several_blocks_per_workgroup(L, N, B, k, splits):
+    """A workgroup that walks several bank blocks: the running best of a query over ascending groups, equal keys in
+    different blocks of one split, more near-identical keys than the two groups that are decided exactly, a short last
+    split."""
+    say(f"match f32 N={N} B={B} k={k} in {splits} splits")
+    g = np.random.Generator(np.random.PCG64(N + B))
+    kn = unit_rows(g, N, k).astype(np.float32)
+    per = -(-((N + 127) // 128) // splits) * 128             # rows of a split
+    assert per >= 256 and N % per > 128                       # several blocks, also in the last split
+    valid = g.random(N) > 0.2
+    base = (0, per, N - N % per)                              # first, second and last split
+    for i, b0 in enumerate(base):
+        # the same key in the split's first and second block; in the second split twice in its second block
+        kn[b0 + 150] = kn[b0 + 7]
+        valid[[b0 + 7, b0 + 150]] = (i != 1, True)
+        if i == 1:
+            kn[b0 + 200] = kn[b0 + 7]
+            valid[b0 + 200] = True
+    for j in (40, 100, 170, 230):                             # a step of fp32 in a few elements: cosines within 1e-6
+        kn[j] = kn[1]
+        kn[j, j % k] = np.nextafter(kn[j, j % k], np.float32(9.0), dtype=np.float32)
+    valid[[1, 40, 100, 170, 230]] = True
+    keys = torch.from_numpy(kn).cuda()
+    bank = make_bank(L, keys, torch.from_numpy(valid.astype(np.uint8)), dtype=torch.float32)
+    qn = unit_rows(g, B, k).astype(np.float32)
+    near = np.concatenate([[b0 + 7 for b0 in base], np.nonzero(valid)[0][-60:]])
+    qn[:len(near)] = kn[near]
+    qn[3:len(near)] += (0.01 * g.standard_normal((len(near) - 3, k))).astype(np.float32)
+    qn[B - 1] = kn[1]
+    q = torch.from_numpy(qn).cuda()
+    qinv = torch.empty((B,), dtype=torch.float32, device="cuda")
+    L.llmc_inv_norm(q, qinv)
+    res = []
+    # 20 bytes per query and split; and the size that is asked for, which leaves the number of splits to the library
+    for size in (20 * B * splits, L.llmc_match_workspace_bytes(bank, B)):
+        ws = torch.empty((size,), dtype=torch.uint8, device="cuda")
+        idx = torch.full((B,), -7, dtype=torch.int32, device="cuda")
+        sim = torch.empty((B,), dtype=torch.float32, device="cuda")
+        hit = torch.empty((B,), dtype=torch.uint8, device="cuda")
+        tie = torch.empty((B,), dtype=torch.uint8, device="cuda")
+        L.llmc_match(bank, q, qinv, 0.9, idx, sim, hit, tie, ws)
+        torch.cuda.synchronize()
+        res.append([npf(x) for x in (idx, sim, hit, tie)])
+    ob = oracle_bank_from_gpu(bank, "f32")
+    oidx, osim = O.match(npf(q), npf(qinv), ob.fp, ob.inv_norm, ob.valid)
+    for idx, sim, hit, tie in res:
+        assert np.all(tie[:B - 1] < 2) and tie[B - 1] == 2    # only the last query has more than two groups in reach
+        assert np.array_equal(idx[:B - 1], oidx[:B - 1])
+        assert idx[:3].tolist() == [7, per + 150, N - N % per + 7]
+        assert np.all(tie[:3] == 1)                           # the runner-up lies in another group of the same split
+        assert int(idx[B - 1]) in (1, 40, 100, 170, 230)
+        assert np.abs(sim - osim).max() < 1e-5
+        assert np.array_equal(hit != 0, osim > 0.9)
+    for a, b in zip(*res):                                    # how the bank is split changes nothing
+        assert np.array_equal(a, b)
     bank.close()
 
 
@@ -1879,7 +1942,8 @@ def test_bf16_layer_tilings(L, arch, d, dff, S, B):
     (64, 64, 1, 1),          # one token, one column tile
     (192, 320, 33, 3),       # 99 tokens: ragged against 32 and 64 rows, widths that are odd multiples of 64
     (128, 64, 145, 2),       # attention: two query blocks and a third of 17, five key tiles, the last with 17 keys
-    (768, 3072, 128, 12),    # 1536 tokens: the feed-forward layers take the wide tiles, the others the small ones
+    (768, 3072, 128, 12),    # 1536 tokens: the wide outputs (2304 and 3072) take the 64 x 64 tiles, the others 32 x 32
+    (768, 3072, 131, 27),    # 3537 tokens, 17 of them in the last row of tiles: 672 tiles of 64 x 64 or more in every layer
 ])
 @pytest.mark.parametrize("arch", [0, 1])
 def test_f32_layer_tilings(L, arch, d, dff, S, B):

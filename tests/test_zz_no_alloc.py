@@ -20,10 +20,10 @@ def unit_rows(g, n, k):
     return x / np.linalg.norm(x, axis=1, keepdims=True)
 
 
-def make_bank(L, N, k, seed, holes=True):
+def make_bank(L, N, k, seed, holes=True, dtype=torch.bfloat16):
     g = np.random.Generator(np.random.PCG64(seed))
-    bank = L.Bank(N, k, 1, 64, torch.bfloat16, "cuda")
-    bank.fp.copy_(torch.from_numpy(unit_rows(g, N, k).astype(np.float32)).to(torch.bfloat16))
+    bank = L.Bank(N, k, 1, 64, dtype, "cuda")
+    bank.fp.copy_(torch.from_numpy(unit_rows(g, N, k).astype(np.float32)).to(dtype))
     L.llmc_inv_norm(bank.fp, bank.inv_norm)
     valid = np.ones(N, np.uint8)
     if holes:
@@ -84,6 +84,31 @@ def test_match_noalloc_rejects_what_does_not_fit():
     with pytest.raises(L.LlmcError) as e:
         L.llmc_match_noalloc(bank, q, qinv, 0.9, idx, None, None, None)
     assert e.value.status == L.ERR_WORKSPACE and "scratch" in str(e.value)
+    torch.cuda.synchronize()
+    assert torch.all(idx == -7)                 # nothing was enqueued
+    bank.close()
+
+
+def test_match_noalloc_f32_takes_every_batch_whose_queries_alone_fit():
+    """fp32 keys: one candidate record (20 bytes) a query is enough, so 262,144 queries are the most that 5 MiB take."""
+    from paper_2512_16843_amd import llmc as L
+    L.lib()
+    N, k = 1000, 32
+    bank, g = make_bank(L, N, k, 5, dtype=torch.float32)
+    most = L.MATCH_STATIC_SCRATCH_BYTES // 20
+    assert most == 262144
+    live = torch.nonzero(bank.valid).flatten()
+    for B in (300, most):
+        say(f"llmc_match_noalloc vs llmc_match, fp32: N={N} B={B} k={k}")
+        want = live[torch.from_numpy(g.integers(0, len(live), B)).cuda()]
+        (i0, s0, h0, t0), (i1, s1, h1, t1) = both(L, bank, bank.fp[want].contiguous(), 0.9)
+        assert torch.equal(i0, i1) and torch.equal(s0, s1) and torch.equal(h0, h1) and torch.equal(t0, t1)
+        assert torch.equal(i1.long(), want) and bool((h1 == 1).all())
+    q = bank.fp[:1].expand(most + 1, k).contiguous()
+    idx = torch.full((most + 1,), -7, dtype=torch.int32, device="cuda")
+    with pytest.raises(L.LlmcError) as e:
+        L.llmc_match_noalloc(bank, q, torch.ones((most + 1,), dtype=torch.float32, device="cuda"), 0.9, idx, None, None, None)
+    assert e.value.status == L.ERR_WORKSPACE
     torch.cuda.synchronize()
     assert torch.all(idx == -7)                 # nothing was enqueued
     bank.close()

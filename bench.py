@@ -98,7 +98,9 @@ def kernel_work(cfg, name, miss, hit, e=2, carry=False, copied=None):
         # with deferred copies only the layers that copy in their reuse step count: copied = (plain, just-in-time)
         rows = float(sum(hit)) if copied is None else float(copied[0])
         return 0.0, 2.0 * rows * S * d * e, "hbm"
-    if name == "materialize_kernel":
+    if name == "compact_materialize_kernel":
+        # the compaction's launch copies the referenced rows that missed; no leg leaves references after the last layer
+        # or runs the divergence monitor, the two other places that copy referenced rows
         return 0.0, 2.0 * float(copied[1] if copied else 0) * S * d * e, "hbm"
     if name == "pool_kernel":
         # stored means carry the reused rows; a post-LayerNorm block pools the rows it computes on the way out

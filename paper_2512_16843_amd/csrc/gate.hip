@@ -148,7 +148,8 @@ __device__ __forceinline__ void gather_body(const u32x4_t* __restrict__ act, con
 // The compaction, and in other workgroups of the same launch the content of the rows to compute that arrived as
 // references (ref_in): which rows those are stands in the hit flags already, so the copies need not wait for the lists.
 // One launch less per layer: an empty one takes 1.6 us in a graph and the copies' usually are empty.  Twelve layers
-// replayed as a graph, all rows answered: 448 -> 423 us, a third of it from faster merges elsewhere.  grid (chunks + 1, B): workgroup (0, 0) compacts, workgroup (c + 1, b) copies chunk c of row b.
+// replayed as a graph, all rows answered: 448 -> 423 us, a third of it from faster merges elsewhere.  grid (chunks + 1,
+// B): workgroup (0, 0) compacts, workgroup (c + 1, b) copies chunk c of row b.
 __global__ __launch_bounds__(1024) void compact_materialize_kernel(
     const uint8_t* __restrict__ hit, const int32_t* __restrict__ idx, const float* __restrict__ sim,
     const uint8_t* __restrict__ tie, int B, float tau, int32_t* __restrict__ hit_rows, int32_t* __restrict__ miss_rows,
@@ -182,7 +183,7 @@ llmc_status_t launch_compact(const uint8_t* d_hit, const int32_t* d_idx, const f
     const size_t vec_per_seq = (size_t)P.S * P.d * elem_size(P.dtype) / 16;
     const size_t per_wg = (size_t)kGatherThreads * kGatherVecPerThread;
     const dim3 grid((unsigned)((vec_per_seq + per_wg - 1) / per_wg) + 1, B);
-    { ProfScope ps_("compact_kernel", st);
+    { ProfScope ps_("compact_materialize_kernel", st);
       LLMC_KERNEL_GGL(compact_materialize_kernel, grid, dim3(1024), 0, st, d_hit, d_idx, d_sim, d_near_tie, B, tau,
                       d_hit_rows, d_miss_rows, d_counters, bank->desc.d_last_used, bank->desc.d_hits, touch, tick,
                       d_pooled_valid_out, has_pool, d_ref_out, bank->desc.d_act_slot, d_ref_in, (const u32x4_t*)P.d_act,

@@ -141,11 +141,6 @@ __device__ __forceinline__ double wave_sum(double v) {
   v = butterfly_add<2>(v);
   return butterfly_add<1>(v);
 }
-__device__ __forceinline__ float wave_max(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
-  return v;
-}
 
 // ---- host-side error plumbing ------------------------------------------------------
 llmc_status_t set_error(llmc_status_t st, const char* fmt, ...);
@@ -239,10 +234,8 @@ llmc_status_t launch_project_rows(const float* d_means, int n_max, int d, int dt
 // token means of B whole sequences, wide form (ws_partials: fingerprint_ws_bytes(B, S, d) bytes), same bits as above
 llmc_status_t launch_pool_means(const void* d_h, int B, int S, int d, int dtype, void* ws_partials, float* d_out,
                                 int ld_out, hipStream_t st);
-// ld_out: floats between consecutive output rows (0: d)
 llmc_status_t launch_pool_rows(const void* d_h, int n_max, int S, int d, int dtype, const int32_t* d_rows,
-                               const int32_t* d_count, const int32_t* d_dst, float* d_out, hipStream_t st,
-                               int ld_out = 0);
+                               const int32_t* d_count, const int32_t* d_dst, float* d_out, hipStream_t st);
 llmc_status_t launch_fingerprint_bits(const void* d_h, int B, int S, int d, int dtype, const void* d_proj,
                                       const float* d_bias, int k, uint32_t* d_bits, void* ws, hipStream_t st,
                                       const float* pooled_in = nullptr, const uint8_t* pooled_valid = nullptr,

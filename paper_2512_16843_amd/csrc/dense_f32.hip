@@ -32,18 +32,19 @@ struct F32Cfg {
   static constexpr size_t LDS_BYTES = (size_t)STAGES * STAGE * 4;
   static_assert(BM % 32 == 0 && BN % 32 == 0 && (STAGES - 2) * L <= 15, "tiling");
 };
-// 32 KiB either way, so that five workgroups share a compute unit and hide each other's waits: deeper rings (48 and
-// 40 KiB, three workgroups) are 2-8 % slower from 512 to 4096 rows, a three-stage small ring 5 % at 128 rows.
+// 32 KiB either way: the launch's four workgroups per compute unit (kF32MaxGrid) are resident together and hide each
+// other's waits.  Deeper rings (48 KiB, of which three fit, and 40 KiB) are 2-8 % slower from 512 to 4096 rows, a
+// three-stage small ring 5 % at 128 rows.
 typedef F32Cfg<64, 64, 2> F32Wide;
 typedef F32Cfg<32, 32, 4> F32Small;
 
 // At most this many 64 x 64 tiles: the launch is cut into 32 x 32 tiles.  A 64 x 64 tile keeps its SIMDs busy four times
-// as long, so with two tiles or fewer per compute unit the last round of them leaves much of the chip idle; beyond
-// that the wide tiles' halved operand traffic wins.  The four linear layers of a 768-wide block, small / wide: 62 / 124 us
+// as long, so with up to two and a half tiles per compute unit the last round of them leaves much of the chip idle;
+// beyond that the wide tiles' halved operand traffic wins.  The four linear layers of a 768-wide block, small / wide: 62 / 124 us
 // at 128 rows, 106 / 152 at 512, 156 (the line) / 183 at 1024; 589 (all below 1024 tiles small) / 514 at 4096, where
 // they reach 113 TFLOP/s.  (512 rows: 96 since a step's fragments are read behind the multiplies of the step before.)
 constexpr int kF32SmallTiles = 640;
-constexpr int kF32MaxGrid = 1024;
+constexpr int kF32MaxGrid = 1024;        // four workgroups for each of 256 compute units
 
 template <class C>
 __device__ __forceinline__ void f32_tiles(const GemmArgs& g, int M, float* lds) {

@@ -354,7 +354,9 @@ __device__ __forceinline__ void gemm_few_tiles(const GemmArgs& g, int M, int tot
 
 // At most this many 32 x 64 tiles in a launch: all of them are resident at once (two workgroups per compute unit).  788
 // rows: 300 tiles of a 768-wide output take 8.0 (K = 768) and 17.2 us (K = 3072) against 8.7 and 20.2 as 78 tiles of
-// 64 x 128; wider outputs at those rows (900 and 1200 tiles) stay with the larger tiles.
+// 64 x 128; wider outputs at those rows (900 and 1200 tiles) stay with the larger tiles.  The four layers of a block
+// together, widths 128 to 2048, with these tiles / without: 19.0 / 20.5 us (128), 26.3 / 42.2 (768) and 49.9 / 90.4
+// (2048) at 64 rows, 17.6 / 20.3, 36.0 / 45.5 and 101 / 114 at 512, 49.7 / 53.1 (768) at 1024.
 constexpr int kGemmFewTiles = 512;
 // at most this many C tiles in a launch: the launch takes CS tiles instead (see the kernel)
 constexpr int kGemmSmallTiles = 256;
@@ -369,6 +371,8 @@ constexpr int kGemmSmallTiles = 256;
 // workgroups have work) and each tile runs its main loop with a deeper ring of its own, because a workgroup that has
 // its compute unit to itself spends a step waiting for that step's loads.  An output element is accumulated over k
 // in the same order by either tiling, so the bits of a row do not depend on how many rows are computed with it.
+// Launch bounds: every tiling counts on two workgroups to a compute unit, which is four wavefronts to a SIMD and at most
+// 128 registers (93 are used, with the bound and without).
 template <class C, class CS>
 __global__ __launch_bounds__(C::THREADS, 4) void gemm_bf16_dma_kernel(GemmArgs g, int tiles_n) {
   static_assert(C::THREADS == CS::THREADS && C::BN == CS::BN, "the two tilings share the launch shape and the column tiles");

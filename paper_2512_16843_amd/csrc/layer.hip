@@ -49,7 +49,9 @@ static llmc_status_t launch_gemm(const GemmArgs& g, int dtype, hipStream_t st) {
       // Every XCD walks its own eighth of the tile list, wide outputs in grouped order; where the column tiles divide by
       // eight, plain striding gives each XCD its own eighth of the COLUMNS instead, so the L2 keeps its weights and only
       // the rows stream (4096 rows, K = 1024: 3072 columns 38.8 -> 33.2 us, 4096 columns 49.6 -> 45.8; 24576 rows of
-      // K = 768 the same either way; 18 column tiles strided 120 us against 114).
+      // K = 768 the same either way; 18 column tiles strided 120 us against 114).  The four layers of a block, strided /
+      // grouped: 146 / 153 us at 4096 rows of 1024 and 501 / 513 of 2048, 1075 / 1058 and 3768 / 3726 at 32768 rows,
+      // equal within the noise for widths of 256 and 512 and for fewer rows.
       a.xcd_chunks = tiles_n <= 8 ? 1 : tiles_n % 8 == 0 ? 0 : 2;
       ProfScope ps_("gemm_bf16_kernel", st);
       LLMC_KERNEL_GGL(kernel, dim3((unsigned)std::min<int64_t>((tiles + 7) & ~7ll, kMaxGrid)), dim3(C::THREADS), lds_bytes, st, a,

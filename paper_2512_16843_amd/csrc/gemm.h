@@ -13,6 +13,16 @@ __device__ __forceinline__ int64_t map_row(const int32_t* rows, int r, int S) {
   const int q = r / S;
   return (int64_t)rows[q] * S + (r - q * S);
 }
+// The same with the division as a multiplication by row_magic(S) = floor(2^61 / S) + 1: exact for r < 2^31, S <= 2^30 (the
+// quotient comes out too large by at most r / 2^61, less than 1 / S).  Five instructions for about thirty: a tile's
+// addresses and its epilogue take a dozen of them, and a small launch runs through its code once, from a cold cache.
+inline uint64_t row_magic(int S) { return (1ull << 61) / (uint64_t)S + 1; }
+__device__ __forceinline__ int64_t map_row(const int32_t* rows, int r, int S, uint64_t magic) {
+  if (!rows) return r;
+  const uint64_t t = (uint64_t)(uint32_t)r * (uint32_t)(magic >> 32) + __umulhi((uint32_t)r, (uint32_t)magic);
+  const int q = (int)(t >> 29);
+  return (int64_t)rows[q] * S + (r - q * S);
+}
 
 // erf by the five-term rational approximation of Abramowitz & Stegun 7.1.26
 // (absolute error below 1.5e-7), with the hardware reciprocal and exponential
@@ -44,11 +54,11 @@ struct GemmArgs {
   int N, K, S;
   const int32_t* count;            // device: number of sequences; null = max_seqs
   int max_seqs;
+  uint64_t s_magic;                // row_magic(S), of the bf16 form
   const int32_t* a_rows;           // sequence list applied to A rows, or null
   const int32_t* r_rows;           // ... to residual rows
   const int32_t* o_rows;           // ... to output rows
   int act;                         // 0 none, 1 GELU erf, 2 GELU tanh
-  int xcd_chunks;                  // tile -> workgroup map of the direct-to-LDS kernel, see there
 };
 
 // the fp32 form (dense_f32.hip)
@@ -61,200 +71,361 @@ __device__ __forceinline__ float apply_act(float v, int act) {
 }
 
 // ---- bf16 GEMM on the matrix cores -------------------------------------------------------
-// bias, activation, residual and (scattered) store of one block's accumulators
-template <class C>
-__device__ __forceinline__ void gemm_epilogue(const GemmArgs& g, f32x16_t (&acc)[C::FM][C::FN], int m0, int n0, int M) {
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const int wm = wave / C::WN, wn = wave % C::WN;
-  const uint16_t* bias = (const uint16_t*)g.bias;
-  const uint16_t* resid = (const uint16_t*)g.resid;
-  uint16_t* out = (uint16_t*)g.out;
+// Workgroups of four wavefronts, two to a compute unit (80 KiB of LDS each), that walk the tiles of a launch.  The product
+// is formed transposed (rows of W are the rows of the matrix instruction's result), so a lane holds outputs of ONE row of
+// `out` and the epilogue needs no LDS.  Every tiling accumulates an output element over k in ascending order with the
+// same instruction, so the bits of a row do not depend on how many rows are computed with it.
+//
+// What bounds it: power first (a loop of nothing but these matrix instructions on such values runs at 1650 TFLOP/s and a
+// clock of 1.7 GHz; with the fragment reads from LDS it reaches 1400, with the loads as well 950 to 1100), so bytes per flop
+// count on every level even where their latency is hidden: a wavefront owns 64 x 96 outputs (64 x 32 before: half the bytes
+// read from LDS), a compute unit two tiles of 128 x 192.  Then the epilogue, which only the other workgroup's main loop
+// covers: an activation chosen at compile time (GELU over 24,576 x 3072 outputs: 186 -> 145 us for the layer).
+// The four layers of a 768-wide block (microseconds, before / now): 24,576 rows 450 / 396, 9984 rows 199 / 178, 8192 rows
+// 171 / 157, 4096 rows 106 / 105, 788 rows 46 / 39, 128 rows 31 / 30; 4096 rows of 1024: 149 / 142.
+// Timed and not taken at 24,576 and 32,768 rows: 256 x 256 tiles with eight wavefronts of 128 x 64 and one workgroup to a
+// compute unit (3 % less at 1024 wide, where the tile count divides by 256, 20 to 60 % more elsewhere); steps of 32 columns
+// with three to five stages (64-byte rows of a panel: 7 to 20 % more); a third stage for A (4 % more).
+
+// what follows the product: 0 nothing, 1 GELU (erf), 2 GELU (tanh), 3 the residual is added
+constexpr int kEpiPlain = 0, kEpiGeluErf = 1, kEpiGeluTanh = 2, kEpiResidual = 3;
+
+template <int EPI>
+__device__ __forceinline__ float gemm_act(float v) {
+  return EPI == kEpiGeluErf ? gelu_erf(v) : EPI == kEpiGeluTanh ? gelu_tanh(v) : v;
+}
+
+// One 32 x 32 fragment of the transposed product, in registers, finished: v[p][0..7] are eight consecutive columns of row
+// p * 16 + lane % 16, at column 16 * (row of 16 lanes % 2) + 8 * (row of 16 lanes / 2) of the fragment, so four lanes
+// cover 64 consecutive bytes of an output row.  Two exchanges of lane halves do it.
+__device__ __forceinline__ int epi_col(int lane) { return (lane >> 4 & 1) * 16 + (lane >> 5) * 8; }
+__device__ __forceinline__ void epi_rows(const f32x16_t& acc, float (&v)[2][8]) {
 #pragma unroll
-  for (int j = 0; j < C::FN; ++j) {
-    const int n = n0 + wn * (C::BN / C::WN) + j * 32 + (lane & 31);
-    if (n >= g.N) continue;
-    const float bv = bias ? bf16_to_f32(bias[n]) : 0.f;
+  for (int p = 0; p < 2; ++p)
 #pragma unroll
-    for (int i = 0; i < C::FM; ++i) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int m = m0 + wm * (C::BM / C::WM) + i * 32 + frag_row(lane, r);
-        if (m >= M) continue;
-        float v = apply_act(acc[i][j][r] + bv, g.act);
-        if (resid) v += bf16_to_f32(resid[map_row(g.r_rows, m, g.S) * g.ldr + n]);
-        out[map_row(g.o_rows, m, g.S) * g.ldo + n] = f32_to_bf16(v);
-      }
+    for (int e = 0; e < 4; ++e) {
+      const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(acc[8 * p + e]), __float_as_uint(acc[8 * p + 4 + e]),
+                                                      false, false);
+      v[p][e] = __uint_as_float(s[0]);
+      v[p][4 + e] = __uint_as_float(s[1]);
     }
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v[0][e]), __float_as_uint(v[1][e]), false, false);
+    v[0][e] = __uint_as_float(s[0]);
+    v[1][e] = __uint_as_float(s[1]);
   }
 }
-
-template <class C>
-__global__ __launch_bounds__(C::THREADS) void gemm_bf16_kernel(GemmArgs g, int tiles_n) {
-  __shared__ __attribute__((aligned(16))) uint16_t lds[C::LDS_BYTES / 2];
-  const int n_seq = g.count ? min(*g.count, g.max_seqs) : g.max_seqs;
-  const int M = n_seq * g.S;
-  const int total = ((M + C::BM - 1) / C::BM) * tiles_n;
-  const int tid = threadIdx.x;
-  // the grid is capped: a workgroup walks tiles blockIdx.x, blockIdx.x + gridDim.x, ...
-  for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
-  const int tile_m = tile / tiles_n, tile_n = tile % tiles_n;
-  const int m0 = tile_m * C::BM, n0 = tile_n * C::BN;
-  const uint16_t* A = (const uint16_t*)g.A;
-  const uint16_t* W = (const uint16_t*)g.W;
-  const uint16_t* a_ptr[C::NLOAD_A];
-  const uint16_t* b_ptr[C::NLOAD_B];
+// bias, activation and residual of eight columns, packed
+template <int EPI>
+__device__ __forceinline__ uint4 epi_finish(float (&v)[8], uint4 bias, uint4 resid) {
+  const uint32_t bw[4] = {bias.x, bias.y, bias.z, bias.w}, rw[4] = {resid.x, resid.y, resid.z, resid.w};
+  uint32_t o[4];
 #pragma unroll
-  for (int i = 0; i < C::NLOAD_A; ++i) {
-    const int v = tid + i * C::THREADS;
-    const int r = min(m0 + v / C::VEC_PER_ROW, M - 1);
-    a_ptr[i] = A + map_row(g.a_rows, r, g.S) * g.lda + (v % C::VEC_PER_ROW) * 8;
+  for (int e = 0; e < 4; ++e) {
+    float lo = gemm_act<EPI>(v[2 * e] + __uint_as_float(bw[e] << 16));
+    float hi = gemm_act<EPI>(v[2 * e + 1] + __uint_as_float(bw[e] & 0xFFFF0000u));
+    if (EPI == kEpiResidual) {
+      lo += __uint_as_float(rw[e] << 16);
+      hi += __uint_as_float(rw[e] & 0xFFFF0000u);
+    }
+    o[e] = f32x2_to_bf16x2(lo, hi);
   }
-#pragma unroll
-  for (int i = 0; i < C::NLOAD_B; ++i) {
-    const int v = tid + i * C::THREADS;
-    const int r = min(n0 + v / C::VEC_PER_ROW, g.N - 1);
-    b_ptr[i] = W + (size_t)r * g.K + (v % C::VEC_PER_ROW) * 8;
-  }
-  f32x16_t acc[C::FM][C::FN];
-#pragma unroll
-  for (int i = 0; i < C::FM; ++i)
-#pragma unroll
-    for (int j = 0; j < C::FN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-  mma_block<C>(a_ptr, b_ptr, g.K, lds, acc);
-  gemm_epilogue<C>(g, acc, m0, n0, M);
-  }
+  return make_uint4(o[0], o[1], o[2], o[3]);
 }
 
-// Epilogue through LDS, one wavefront at a time: a wavefront lays 16 rows of its accumulators (half a fragment:
-// registers 8 h .. 8 h + 7 hold rows 16 h .. 16 h + 15 of it) out as fp32 [16][FN * 32 + 4] in a region of its own,
-// then its lanes take 8 consecutive columns of a row each, so that bias, residual and output move as 16-byte
-// vectors along rows.  No other wavefront touches the region, and LDS operations of one wavefront complete in
-// order, so no barrier is needed between the two halves.  Blocks of 16 rows keep the staging of all wavefronts
-// inside ONE ring stage, so the other stage can already receive the next tile's first loads.  `stage` is that
-// ring stage; no barrier inside or after: the next tile's first barrier comes before anything is loaded into this
-// stage again.
-template <class C>
-struct WaveEpilogue16 {
-  static constexpr int COLS = C::FN * 32, STRIDE = COLS + 4, REGION = 16 * STRIDE;   // floats
-  static constexpr int LANES_PER_ROW = COLS / 8, ROWS_PER_PASS = 64 / LANES_PER_ROW;
-  static_assert(64 % LANES_PER_ROW == 0 && 16 % ROWS_PER_PASS == 0, "row vectors tile the block");
-  static_assert((size_t)C::NW * REGION * 4 <= (size_t)C::STAGE_ELEMS * 2, "the staging fits one ring stage");
+// LDS stage of a 64-column step: BM rows of A, then BN rows of W, 128 bytes each; the eight 16-byte chunks of row r lie
+// XOR-swizzled by r / 2 (see mma.h).  A wavefront's load fetches eight rows, `gemm_chunk` is the lane's element offset.
+__device__ __forceinline__ int gemm_chunk(int tr, int lane) { return ((lane & 7) ^ ((tr >> 1) & 7)) * 8; }
+// element offset of a lane's fragment chunk of 16-column sub-step ks within its row
+__device__ __forceinline__ int gemm_slot(int ks, int lane) { return ((ks * 2 + (lane >> 5)) ^ ((lane >> 1) & 7)) * 8; }
+
+// ---- many rows -------------------------------------------------------------------------------------------
+// 2 x 2 wavefronts, each (BM / 2) x (BN / 2) outputs, and a ring of two 64-column stages that runs on across the tiles of a
+// workgroup: the loads of the next tile start two steps before this one ends.  The refill of a stage is issued behind the
+// first two multiplies after the barrier, not in front of them (10 % of the loop's time).
+template <int BM_, int BN_>
+struct GemmRing {
+  static constexpr int BM = BM_, BN = BN_, BK = 64, NW = 4;
+  static constexpr int FM = BM / 64, FN = BN / 64;                 // 32 x 32 fragments of a wavefront
+  static constexpr int LA = BM / 8 / NW, LB = BN / 8 / NW;         // its loads of a stage
+  static constexpr int STAGE = (BM + BN) * BK;
+  static constexpr size_t LDS_BYTES = 2ull * STAGE * 2;
+  static_assert(BM % 64 == 0 && BN % 64 == 0 && FM * FN >= 2, "fragments");
 };
 
-template <class C>
-__device__ __forceinline__ void gemm_epilogue_wave16(const GemmArgs& g, f32x16_t (&acc)[C::FM][C::FN], int m0, int n0,
-                                                     int M, float* stage, bool wait_before_last) {
-  using E = WaveEpilogue16<C>;
+template <class C, int EPI>
+__device__ __forceinline__ void gemm_ring_tiles(const GemmArgs& g, int M, uint16_t* lds) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int wm = wave / C::WN, wn = wave % C::WN;
-  float* region = stage + wave * E::REGION;
+  const int wm = wave >> 1, wn = wave & 1;
+  const int tiles_n = (g.N + C::BN - 1) / C::BN, tiles_m = (M + C::BM - 1) / C::BM, total = tiles_m * tiles_n;
+  const uint16_t* A = (const uint16_t*)g.A;
+  const uint16_t* W = (const uint16_t*)g.W;
   const uint16_t* bias = (const uint16_t*)g.bias;
   const uint16_t* resid = (const uint16_t*)g.resid;
   uint16_t* out = (uint16_t*)g.out;
-  const int prow = lane / E::LANES_PER_ROW, c8 = (lane % E::LANES_PER_ROW) * 8;
-  const int n = n0 + wn * E::COLS + c8;
-  float bv[8];
+  const int nk = g.K / C::BK;
+  // Workgroups are dealt round-robin to the 8 XCDs, each with an L2 of its own.  XCD x walks the x-th eighth of the tile
+  // list, so that neighbouring tiles share their operand panels there: row by row for narrow outputs; wide outputs down
+  // eight row blocks before the list moves one column tile on.  Where the column tiles divide by eight, plain striding
+  // gives every XCD its own eighth of the columns instead: its L2 keeps those rows of W and only A streams.
+  const int order = tiles_n <= 8 ? 1 : tiles_n % 8 == 0 ? 0 : 2;
+  const int xcd = blockIdx.x & 7, per_xcd = (total + 7) >> 3;
+  const int it_step = order ? (int)(gridDim.x >> 3) : (int)gridDim.x;
+  auto locate = [&](int it, int& m, int& n) -> bool {
+    if (order && it >= per_xcd) return false;
+    const int tile = order ? xcd * per_xcd + it : it;
+    if (tile >= total) return false;
+    int tile_m = tile / tiles_n, tile_n = tile % tiles_n;
+    if (order == 2) {
+      const int group = tile / (8 * tiles_n), in_group = tile % (8 * tiles_n);
+      const int rows_in_group = min(8, tiles_m - group * 8);
+      tile_m = group * 8 + in_group % rows_in_group;
+      tile_n = in_group / rows_in_group;
+    }
+    m = tile_m * C::BM;
+    n = tile_n * C::BN;
+    return true;
+  };
+  int it = order ? (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+  int m0 = 0, n0 = 0;
+  if (!locate(it, m0, n0)) return;
+
+  // the load side: position, and this lane's addresses in the tile it stands in
+  const uint16_t* a_ptr[C::LA];
+  const uint16_t* b_ptr[C::LB];
+  auto address = [&](int m, int n) {
 #pragma unroll
-  for (int e = 0; e < 8; ++e) bv[e] = 0.f;
-  if (bias && n < g.N) Vec16<bf16_t>::load(reinterpret_cast<const bf16_t*>(bias + n), bv);
+    for (int j = 0; j < C::LA; ++j) {
+      const int tr = (j * C::NW + wave) * 8 + (lane >> 3);
+      a_ptr[j] = A + map_row(g.a_rows, min(m + tr, M - 1), g.S, g.s_magic) * g.lda + gemm_chunk(tr, lane);
+    }
 #pragma unroll
-  for (int i = 0; i < C::FM; ++i) {
+    for (int j = 0; j < C::LB; ++j) {
+      const int tr = (j * C::NW + wave) * 8 + (lane >> 3);
+      b_ptr[j] = W + (size_t)min(n + tr, g.N - 1) * g.K + gemm_chunk(tr, lane);
+    }
+  };
+  address(m0, n0);
+  int kl = 0, fill = 0;
+  bool live = true;
+  auto issue_b = [&]() {
+    if (kl == nk) {
+      int m, n;
+      kl = 0;
+      live = locate(it + it_step, m, n);
+      if (live) address(m, n);
+    }
+    if (!live) return;
+    uint16_t* st = lds + fill * C::STAGE + C::BM * C::BK;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
+    for (int j = 0; j < C::LB; ++j)
+      __builtin_amdgcn_global_load_lds(LLMC_GPTR(b_ptr[j] + kl * C::BK), LLMC_LPTR(st + (j * C::NW + wave) * 512), 16, 0, 0);
+  };
+  auto issue_a = [&]() {
+    if (!live) return;
+    uint16_t* st = lds + fill * C::STAGE;
 #pragma unroll
-      for (int j = 0; j < C::FN; ++j) {
-        float* p = region + j * 32 + (lane & 31);
+    for (int j = 0; j < C::LA; ++j)
+      __builtin_amdgcn_global_load_lds(LLMC_GPTR(a_ptr[j] + kl * C::BK), LLMC_LPTR(st + (j * C::NW + wave) * 512), 16, 0, 0);
+    fill ^= 1;
+    ++kl;
+  };
+
+  int sw[4];
 #pragma unroll
-        for (int r = 0; r < 8; ++r) p[(frag_row(lane, 8 * h + r) - 16 * h) * E::STRIDE] = acc[i][j][8 * h + r];
-      }
-      const int mb = m0 + wm * (C::BM / C::WM) + i * 32 + h * 16;
+  for (int ks = 0; ks < 4; ++ks) sw[ks] = gemm_slot(ks, lane);
+  const int a_row = (wm * (C::BM / 2) + (lane & 31)) * C::BK;
+  const int b_row = (C::BM + wn * (C::BN / 2) + (lane & 31)) * C::BK;
+  bf16x8_t fa[2][C::FM], fb[2][C::FN];
+  int stage = 0;
+  auto read = [&](int ks, int buf) {
+    const uint16_t* st = lds + stage * C::STAGE + sw[ks];
 #pragma unroll
-      for (int pass = 0; pass < 16 / E::ROWS_PER_PASS; ++pass) {
-        const int row = pass * E::ROWS_PER_PASS + prow;
-        const int m = mb + row;
-        const float4 lo = *reinterpret_cast<const float4*>(region + row * E::STRIDE + c8);
-        const float4 hi = *reinterpret_cast<const float4*>(region + row * E::STRIDE + c8 + 4);
-        const bool live = m < M && n < g.N;
-        float v[8] = {lo.x + bv[0], lo.y + bv[1], lo.z + bv[2], lo.w + bv[3],
-                      hi.x + bv[4], hi.y + bv[5], hi.z + bv[6], hi.w + bv[7]};
-        if (g.act) {
+    for (int i = 0; i < C::FN; ++i) fb[buf][i] = *reinterpret_cast<const bf16x8_t*>(st + b_row + i * 32 * C::BK);
 #pragma unroll
-          for (int e = 0; e < 8; ++e) v[e] = apply_act(v[e], g.act);
+    for (int j = 0; j < C::FM; ++j) fa[buf][j] = *reinterpret_cast<const bf16x8_t*>(st + a_row + j * 32 * C::BK);
+  };
+
+  // this lane's columns and rows of the epilogue; bias and the first rows of the residual are fetched two steps early
+  const int col = wn * (C::BN / 2) + epi_col(lane), row = wm * (C::BM / 2) + (lane & 15);
+  uint4 bq[C::FN], rq[2][C::FN];
+  auto load_resid = [&](int j, int i0, int i1) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const uint16_t* src = resid + map_row(g.r_rows, min(m0 + row + j * 32 + p * 16, M - 1), g.S, g.s_magic) * g.ldr;
+#pragma unroll
+      for (int i = 0; i < C::FN; ++i)
+        if (i >= i0 && i < i1) rq[p][i] = *reinterpret_cast<const uint4*>(src + min(n0 + col + i * 32, g.N - 8));
+    }
+  };
+#pragma unroll
+  for (int i = 0; i < C::FN; ++i) bq[i] = rq[0][i] = rq[1][i] = make_uint4(0, 0, 0, 0);
+
+  issue_b(); issue_a();
+  issue_b(); issue_a();                                     // nk >= 2
+  LLMC_WAIT_VM(C::LA + C::LB);
+  dma::barrier();
+  read(0, 0);
+  bool first = true;
+  while (true) {
+    f32x16_t acc[C::FN][C::FM];
+#pragma unroll
+    for (int i = 0; i < C::FN; ++i)
+#pragma unroll
+      for (int j = 0; j < C::FM; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int kt = 0; kt < nk; ++kt) {
+#pragma unroll
+      for (int ks = 0; ks < 4; ++ks) {
+        const int c = ks & 1;
+        // this sub-step's fragments were requested one sub-step ago
+        __builtin_amdgcn_sched_barrier(0);
+        LLMC_WAIT_LGKM(0);
+        __builtin_amdgcn_sched_barrier(0);
+        if (ks == 3) {
+          // The step's last fragments are in registers: its stage is free once everybody stands here, and everybody's loads
+          // of the next step have landed (of a tile's second step: waited for before the stores of the tile before).
+          if (kt > 0 || first) LLMC_WAIT_VM(0);
+          dma::barrier();
+          stage ^= 1;
+          read(0, c ^ 1);                                   // behind the last tile: old contents, not used
+          if (kt + 2 == nk) {
+            if (bias) {
+#pragma unroll
+              for (int i = 0; i < C::FN; ++i) bq[i] = *reinterpret_cast<const uint4*>(bias + min(n0 + col + i * 32, g.N - 8));
+            }
+            if (EPI == kEpiResidual) load_resid(0, 0, 2);    // a third column of fragments: registers
+          }
+        } else {
+          read(ks + 1, c ^ 1);
         }
-        if (resid && live) {
-          float rr[8];
-          Vec16<bf16_t>::load(reinterpret_cast<const bf16_t*>(resid + map_row(g.r_rows, m, g.S) * g.ldr + n), rr);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-          for (int e = 0; e < 8; ++e) v[e] += rr[e];
-        }
-        // before the LAST stores of the tile: everything this wavefront has in flight has landed, in particular its
-        // loads of the next tile's first step (issued before this epilogue began); the stores below are then the
-        // only traffic outstanding when the next tile's main loop starts, and its first step does not wait for them
-        if (wait_before_last && i == C::FM - 1 && h == 1 && pass == 16 / E::ROWS_PER_PASS - 1) LLMC_WAIT_VM(0);
-        if (live) Vec16<bf16_t>::store(reinterpret_cast<bf16_t*>(out + map_row(g.o_rows, m, g.S) * g.ldo + n), v);
+        for (int i = 0; i < C::FN; ++i)
+#pragma unroll
+          for (int j = 0; j < C::FM; ++j) {
+            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[c][i], fa[c][j], acc[i][j], 0, 0, 0);
+            // the loads that refill the stage are issued behind the first multiplies, not in front of them
+            if (ks == 3 && i * C::FM + j < 2) {
+              __builtin_amdgcn_sched_barrier(0);
+              if (i * C::FM + j == 0) issue_b();
+              else issue_a();
+              __builtin_amdgcn_sched_barrier(0);
+            }
+          }
       }
     }
+    first = false;
+    if (EPI == kEpiResidual) load_resid(0, 2, C::FN);
+    // the finished values are packed into the registers of the sums: two rows of 16-byte vectors in registers 0..7
+#pragma unroll
+    for (int j = 0; j < C::FM; ++j) {
+#pragma unroll
+      for (int i = 0; i < C::FN; ++i) {
+        float v[2][8];
+        epi_rows(acc[i][j], v);
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+          const uint4 o = epi_finish<EPI>(v[p], bq[i], rq[p][i]);
+          acc[i][j][4 * p] = __uint_as_float(o.x);
+          acc[i][j][4 * p + 1] = __uint_as_float(o.y);
+          acc[i][j][4 * p + 2] = __uint_as_float(o.z);
+          acc[i][j][4 * p + 3] = __uint_as_float(o.w);
+        }
+        __builtin_amdgcn_sched_barrier(0);                    // one fragment at a time: registers
+      }
+      if (EPI == kEpiResidual && j + 1 < C::FM) load_resid(j + 1, 0, C::FN);
+    }
+    // This wavefront's loads of the next tile have landed before its stores go out: the next tile's first steps wait for
+    // neither.
+    LLMC_WAIT_VM(0);
+#pragma unroll
+    for (int j = 0; j < C::FM; ++j)
+#pragma unroll
+      for (int p = 0; p < 2; ++p) {
+        const int m = m0 + row + j * 32 + p * 16;
+        if (m < M) {
+          uint16_t* dst = out + map_row(g.o_rows, m, g.S, g.s_magic) * g.ldo;
+#pragma unroll
+          for (int i = 0; i < C::FN; ++i) {
+            const int n = n0 + col + i * 32;
+            if (n < g.N)
+              *reinterpret_cast<uint4*>(dst + n) =
+                  make_uint4(__float_as_uint(acc[i][j][4 * p]), __float_as_uint(acc[i][j][4 * p + 1]),
+                             __float_as_uint(acc[i][j][4 * p + 2]), __float_as_uint(acc[i][j][4 * p + 3]));
+          }
+        }
+      }
+    it += it_step;
+    if (!locate(it, m0, n0)) return;
   }
 }
 
-template <class C, class CS>
-constexpr size_t gemm_dma_smem_bytes() {
-  return C::LDS_BYTES > CS::LDS_BYTES ? C::LDS_BYTES : CS::LDS_BYTES;   // GemmFew: as much as CS
-}
-
-// ---- a handful of rows ---------------------------------------------------------------------------
-// With few rows a launch is one pass over k by a few workgroups and its time is the latency of the loads over the
-// number of steps in flight.  So: 32 x 64 tiles (four times the workgroups of 64 x 128, each a quarter of the work
-// of its compute unit) and a ring of six 12 KiB stages, five steps of 64 k ahead, in the LDS of the launch.  All
-// eight wavefronts load (a stage is twelve blocks of eight rows: wavefronts 0..3 fetch two, the others one), the first
-// two multiply, one 32 x 32 fragment each.  An element is accumulated over k in the order of the other tilings.
-// At 128 rows of a 768-wide block (64 x 128 tiles with three stages before): QKV 8.0 -> 5.5 us, output projection 8.1 ->
-// 5.9, feed-forward 9.1 -> 6.9 and 20.0 -> 11.1, of which an empty launch is 4.  The loop below matters as much as the
-// tile: with every fragment read waited for before its own multiply the last of them took 23.4 us.
-struct GemmFew {
-  static constexpr int BM = 32, BN = 64, BK = 64, STAGES = 6;
-  static constexpr int STAGE_ELEMS = (BM + BN) * BK;
-  static constexpr size_t LDS_BYTES = (size_t)STAGES * STAGE_ELEMS * 2;
+// ---- fewer rows: a ring of its own per tile ----------------------------------------------------------------
+// A launch with few tiles lasts as long as the latency of its loads times the steps over the steps in flight, and a
+// step as long as its own fragments take to arrive from LDS.  (788 rows of a 768-wide block: 17.7 -> 12.8 us for K = 3072.)  So: smaller tiles, more stages, and a whole step's
+// fragments held in registers: those of step kt are read from LDS behind the multiplies of step kt - 1 that free theirs.
+// WM x WN wavefronts multiply (they fetch PC blocks of eight rows a stage), the others only load (PL blocks).
+template <int BM_, int BN_, int WM_, int WN_, int STAGES_, int PC_, int PL_>
+struct GemmStep {
+  static constexpr int BM = BM_, BN = BN_, WM = WM_, WN = WN_, BK = 64, STAGES = STAGES_, PC = PC_, PL = PL_, NW = 4;
+  static constexpr int FM = BM / WM / 32, FN = BN / WN / 32, COMPUTE = WM * WN;
+  static constexpr int STAGE = (BM + BN) * BK;
+  static constexpr size_t LDS_BYTES = (size_t)STAGES * STAGE * 2;
+  static_assert(COMPUTE * PC + (NW - COMPUTE) * PL == (BM + BN) / 8, "the blocks of a stage");
+  static_assert(STAGES >= 3 && STAGES <= 6, "the waits of the loop");
 };
 
-// The k loop of one wavefront: PER loads a step; COMPUTE: it multiplies too.  The fragments of step kt are read from LDS
-// behind the multiplies of step kt - 1 that free their registers, so a step does not cost the sum of the two.
-template <int PER, bool COMPUTE>
-__device__ __forceinline__ void gemm_few_loop(const uint16_t* p0, const uint16_t* p1, int nk, int wave, uint16_t* lds,
-                                              int a_row, int b_row, const int (&sw)[4], f32x16_t& acc) {
-  using C = GemmFew;
+// The k loop of one wavefront that fetches PER blocks a step and, with MUL, multiplies.
+template <class C, int PER, bool MUL>
+__device__ __forceinline__ void gemm_step_loop(const uint16_t* const (&src)[PER], int first_block, int nk, uint16_t* lds,
+                                               int a_row, int b_row, const int (&sw)[4], f32x16_t (&acc)[C::FN][C::FM]) {
   int in = 0, rd = 0;                                        // ring stages of the next load and of the next read
   auto issue = [&](int kt) {
-    uint16_t* st = lds + in * C::STAGE_ELEMS;
+    uint16_t* st = lds + in * C::STAGE + first_block * 512;
     in = in + 1 == C::STAGES ? 0 : in + 1;
-    __builtin_amdgcn_global_load_lds(LLMC_GPTR(p0 + kt * C::BK), LLMC_LPTR(st + wave * 8 * C::BK), 16, 0, 0);
-    if (PER == 2)
-      __builtin_amdgcn_global_load_lds(LLMC_GPTR(p1 + kt * C::BK), LLMC_LPTR(st + (8 + wave) * 8 * C::BK), 16, 0, 0);
-  };
-  bf16x8_t fa[4], fb[4];                                     // zeros until the first step has been read
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) fa[ks] = fb[ks] = bf16x8_t{};
+    for (int j = 0; j < PER; ++j)
+      __builtin_amdgcn_global_load_lds(LLMC_GPTR(src[j] + kt * C::BK), LLMC_LPTR(st + j * 512), 16, 0, 0);
+  };
+  bf16x8_t fa[4][C::FM], fb[4][C::FN];                       // zeros until the first step has been read
+#pragma unroll
+  for (int ks = 0; ks < 4; ++ks) {
+#pragma unroll
+    for (int j = 0; j < C::FM; ++j) fa[ks][j] = bf16x8_t{};
+#pragma unroll
+    for (int i = 0; i < C::FN; ++i) fb[ks][i] = bf16x8_t{};
+  }
+  auto mul = [&](int ks) {
+#pragma unroll
+    for (int i = 0; i < C::FN; ++i)
+#pragma unroll
+      for (int j = 0; j < C::FM; ++j)
+        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[ks][i], fa[ks][j], acc[i][j], 0, 0, 0);
+  };
   // everybody's loads of this step have landed, and everybody has its fragments of the step before
   auto step = [&](int kt, bool more) {
-    if (COMPUTE) LLMC_WAIT_LGKM(0);
+    if (MUL) LLMC_WAIT_LGKM(0);
     dma::barrier();
     if (more) issue(kt + C::STAGES - 1);
-    if (COMPUTE) {
-      const uint16_t* st = lds + rd * C::STAGE_ELEMS;
+    if (MUL) {
+      const uint16_t* st = lds + rd * C::STAGE;
       rd = rd + 1 == C::STAGES ? 0 : rd + 1;
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks) {
-        acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks], fb[ks], acc, 0, 0, 0);
-        fa[ks] = *reinterpret_cast<const bf16x8_t*>(st + a_row + sw[ks]);
-        fb[ks] = *reinterpret_cast<const bf16x8_t*>(st + b_row + sw[ks]);
+        mul(ks);
+#pragma unroll
+        for (int i = 0; i < C::FN; ++i) fb[ks][i] = *reinterpret_cast<const bf16x8_t*>(st + b_row + i * 32 * C::BK + sw[ks]);
+#pragma unroll
+        for (int j = 0; j < C::FM; ++j) fa[ks][j] = *reinterpret_cast<const bf16x8_t*>(st + a_row + j * 32 * C::BK + sw[ks]);
         __builtin_amdgcn_sched_barrier(0);
       }
     }
   };
+#pragma unroll
   for (int s = 0; s < C::STAGES - 1; ++s)
     if (s < nk) issue(s);
   int kt = 0;
@@ -264,29 +435,30 @@ __device__ __forceinline__ void gemm_few_loop(const uint16_t* p0, const uint16_t
   }
   auto tail = [&](auto steps) {
     constexpr int ahead = decltype(steps)::value;
-    if (kt == nk - 1 - ahead) {                              // not for every one when nk < STAGES - 1
+    if (ahead <= C::STAGES - 2 && kt == nk - 1 - ahead) {    // not for every one when nk < STAGES - 1
       LLMC_WAIT_VM(ahead * PER);
       step(kt, false);
       ++kt;
     }
   };
-  static_assert(C::STAGES == 6, "the steps of the tail");
   tail(std::integral_constant<int, 4>());
   tail(std::integral_constant<int, 3>());
   tail(std::integral_constant<int, 2>());
   tail(std::integral_constant<int, 1>());
   tail(std::integral_constant<int, 0>());
-  if (COMPUTE) {
+  if (MUL) {
     LLMC_WAIT_LGKM(0);           // the last fragments are in registers before the caller's barrier hands their stage on
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[ks], fb[ks], acc, 0, 0, 0);
+    for (int ks = 0; ks < 4; ++ks) mul(ks);
   }
 }
 
-__device__ __forceinline__ void gemm_few_tiles(const GemmArgs& g, int M, int total, int tiles_n, uint16_t* lds) {
-  using C = GemmFew;
+template <class C, int EPI>
+__device__ __forceinline__ void gemm_step_tiles(const GemmArgs& g, int M, uint16_t* lds) {
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wm = wave / C::WN, wn = wave % C::WN;            // of the multiplying wavefronts
+  const int tiles_n = (g.N + C::BN - 1) / C::BN, total = ((M + C::BM - 1) / C::BM) * tiles_n;
   const uint16_t* A = (const uint16_t*)g.A;
   const uint16_t* W = (const uint16_t*)g.W;
   const uint16_t* bias = (const uint16_t*)g.bias;
@@ -295,199 +467,133 @@ __device__ __forceinline__ void gemm_few_tiles(const GemmArgs& g, int M, int tot
   const int nk = g.K / C::BK;
   int sw[4];
 #pragma unroll
-  for (int ks = 0; ks < 4; ++ks) sw[ks] = (((ks * 2 + (lane >> 5)) ^ ((lane >> 1) & 7)) * 8);
-  const int a_row = (lane & 31) * C::BK;
-  const int b_row = (C::BM + wave * 32 + (lane & 31)) * C::BK;          // of the multiplying wavefronts
+  for (int ks = 0; ks < 4; ++ks) sw[ks] = gemm_slot(ks, lane);
+  const int a_row = (wm * (C::BM / C::WM) + (lane & 31)) * C::BK;
+  const int b_row = (C::BM + wn * (C::BN / C::WN) + (lane & 31)) * C::BK;
   for (int tile = blockIdx.x; tile < total; tile += gridDim.x) {
     const int m0 = (tile / tiles_n) * C::BM, n0 = (tile % tiles_n) * C::BN;
-    // block `wave` of a stage, and block 8 + wave for wavefronts 0..3: blocks 0..3 are rows of A, 4..11 rows of W
-    auto source = [&](int block) -> const uint16_t* {
+    auto source = [&](int block) -> const uint16_t* {        // blocks 0 .. BM / 8 - 1 are rows of A, the others rows of W
       const int tr = block * 8 + (lane >> 3);
-      const int chunk = ((lane & 7) ^ ((tr >> 1) & 7)) * 8;
-      if (block < 4) return A + map_row(g.a_rows, min(m0 + tr, M - 1), g.S) * g.lda + chunk;
-      return W + (size_t)min(n0 + tr - C::BM, g.N - 1) * g.K + chunk;
+      if (block < C::BM / 8) return A + map_row(g.a_rows, min(m0 + tr, M - 1), g.S, g.s_magic) * g.lda + gemm_chunk(tr, lane);
+      return W + (size_t)min(n0 + tr - C::BM, g.N - 1) * g.K + gemm_chunk(tr, lane);
     };
-    const uint16_t* p0 = source(wave);
-    const uint16_t* p1 = wave < 4 ? source(8 + wave) : p0;
-    f32x16_t acc;
+    if (wave < C::COMPUTE) {
+      const uint16_t* src[C::PC];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-    if (wave < 2) gemm_few_loop<2, true>(p0, p1, nk, wave, lds, a_row, b_row, sw, acc);
-    else if (wave < 4) gemm_few_loop<2, false>(p0, p1, nk, wave, lds, a_row, b_row, sw, acc);
-    else gemm_few_loop<1, false>(p0, p1, nk, wave, lds, a_row, b_row, sw, acc);
-    dma::barrier();               // every fragment has been read: the first stage takes the staging of the epilogue
-    if (wave < 2) {
-      // 32 x 32 fp32 laid out by row, then four lanes take a row each, 8 consecutive columns a lane
-      float* region = reinterpret_cast<float*>(lds) + wave * 32 * 36;
+      for (int j = 0; j < C::PC; ++j) src[j] = source(wave * C::PC + j);
+      // bias and residual are on their way before the first step: behind the last one each would cost its latency
+      const int n = n0 + wn * (C::BN / C::WN) + epi_col(lane), m = m0 + wm * (C::BM / C::WM) + (lane & 15);
+      uint4 bq[C::FN], rq[C::FN][C::FM][2];
 #pragma unroll
-      for (int r = 0; r < 16; ++r) region[frag_row(lane, r) * 36 + (lane & 31)] = acc[r];
-      const int c8 = (lane & 3) * 8, n = n0 + wave * 32 + c8;
-      float bv[8];
+      for (int i = 0; i < C::FN; ++i) {
+        bq[i] = bias ? *reinterpret_cast<const uint4*>(bias + min(n + i * 32, g.N - 8)) : make_uint4(0, 0, 0, 0);
 #pragma unroll
-      for (int e = 0; e < 8; ++e) bv[e] = 0.f;
-      if (bias && n < g.N) Vec16<bf16_t>::load(reinterpret_cast<const bf16_t*>(bias + n), bv);
+        for (int j = 0; j < C::FM; ++j)
 #pragma unroll
-      for (int pass = 0; pass < 2; ++pass) {
-        const int row = pass * 16 + (lane >> 2), m = m0 + row;
-        const float4 lo = *reinterpret_cast<const float4*>(region + row * 36 + c8);
-        const float4 hi = *reinterpret_cast<const float4*>(region + row * 36 + c8 + 4);
-        if (m < M && n < g.N) {
-          float v[8] = {lo.x + bv[0], lo.y + bv[1], lo.z + bv[2], lo.w + bv[3],
-                        hi.x + bv[4], hi.y + bv[5], hi.z + bv[6], hi.w + bv[7]};
-          if (g.act) {
+          for (int p = 0; p < 2; ++p) rq[i][j][p] = make_uint4(0, 0, 0, 0);
+      }
+      if (EPI == kEpiResidual) {
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] = apply_act(v[e], g.act);
+        for (int j = 0; j < C::FM; ++j)
+#pragma unroll
+          for (int p = 0; p < 2; ++p) {
+            const uint16_t* row = resid + map_row(g.r_rows, min(m + j * 32 + p * 16, M - 1), g.S, g.s_magic) * g.ldr;
+#pragma unroll
+            for (int i = 0; i < C::FN; ++i) rq[i][j][p] = *reinterpret_cast<const uint4*>(row + min(n + i * 32, g.N - 8));
           }
-          if (resid) {
-            float rr[8];
-            Vec16<bf16_t>::load(reinterpret_cast<const bf16_t*>(resid + map_row(g.r_rows, m, g.S) * g.ldr + n), rr);
+      }
+      f32x16_t acc[C::FN][C::FM];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) v[e] += rr[e];
+      for (int i = 0; i < C::FN; ++i)
+#pragma unroll
+        for (int j = 0; j < C::FM; ++j)
+#pragma unroll
+          for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+      gemm_step_loop<C, C::PC, true>(src, wave * C::PC, nk, lds, a_row, b_row, sw, acc);
+#pragma unroll
+      for (int j = 0; j < C::FM; ++j) {
+        uint16_t* dst[2];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) dst[p] = out + map_row(g.o_rows, min(m + j * 32 + p * 16, M - 1), g.S, g.s_magic) * g.ldo + n;
+#pragma unroll
+        for (int i = 0; i < C::FN; ++i) {
+          float v[2][8];
+          epi_rows(acc[i][j], v);
+#pragma unroll
+          for (int p = 0; p < 2; ++p) {
+            const uint4 o = epi_finish<EPI>(v[p], bq[i], rq[i][j][p]);
+            if (m + j * 32 + p * 16 < M && n + i * 32 < g.N) *reinterpret_cast<uint4*>(dst[p] + i * 32) = o;
           }
-          Vec16<bf16_t>::store(reinterpret_cast<bf16_t*>(out + map_row(g.o_rows, m, g.S) * g.ldo + n), v);
         }
       }
+    } else if constexpr (C::COMPUTE < C::NW) {
+      const int b0 = C::COMPUTE * C::PC + (wave - C::COMPUTE) * C::PL;
+      const uint16_t* src[C::PL];
+#pragma unroll
+      for (int j = 0; j < C::PL; ++j) src[j] = source(b0 + j);
+      f32x16_t none[C::FN][C::FM];
+      gemm_step_loop<C, C::PL, false>(src, b0, nk, lds, a_row, b_row, sw, none);
     }
-    dma::barrier();               // ... and is read out before the next tile's first loads land there
+    dma::barrier();               // every fragment has been read before the next tile's first loads land
   }
 }
 
-// At most this many 32 x 64 tiles in a launch: all of them are resident at once (two workgroups per compute unit).  788
-// rows: 300 tiles of a 768-wide output take 8.0 (K = 768) and 17.2 us (K = 3072) against 8.7 and 20.2 as 78 tiles of
-// 64 x 128; wider outputs at those rows (900 and 1200 tiles) stay with the larger tiles.  The four layers of a block
-// together, widths 128 to 2048, with these tiles / without: 19.0 / 20.5 us (128), 26.3 / 42.2 (768) and 49.9 / 90.4
-// (2048) at 64 rows, 17.6 / 20.3, 36.0 / 45.5 and 101 / 114 at 512, 49.7 / 53.1 (768) at 1024.
-constexpr int kGemmFewTiles = 512;
-// at most this many C tiles in a launch: the launch takes CS tiles instead (see the kernel)
-constexpr int kGemmSmallTiles = 256;
+// ---- the kernel: which tiling a launch takes ----------------------------------------------------------------
+typedef GemmRing<128, 192> GemmBig;                    // 80 KiB
+typedef GemmRing<128, 128> GemmMid;                    // 64 KiB
+typedef GemmStep<64, 128, 2, 2, 3, 6, 6> GemmLow;      // 72 KiB
+typedef GemmStep<64, 64, 2, 2, 4, 4, 4> GemmTiny;      // 64 KiB
+typedef GemmStep<32, 64, 1, 2, 6, 2, 4> GemmFew;       // 72 KiB
+constexpr size_t kGemmLdsBytes = GemmBig::LDS_BYTES;
+constexpr int kGemmGrid = 512;                         // two workgroups on each of 256 compute units
+static_assert(GemmMid::LDS_BYTES <= kGemmLdsBytes && GemmLow::LDS_BYTES <= kGemmLdsBytes &&
+              GemmTiny::LDS_BYTES <= kGemmLdsBytes && GemmFew::LDS_BYTES <= kGemmLdsBytes, "one launch serves all tilings");
 
-// Same contract, main loop with direct global -> LDS loads (C is a DmaCfg with two stages); K % 64 == 0.
-// A workgroup walks its tiles with ONE ring of two stages that runs on across tiles: when the main loop of a tile
-// ends, the first loads of the workgroup's next tile go into the stage that is free, and only then does the epilogue
-// start (its staging lives in the stage the last step has just been read from), so the memory latency of a tile's
-// first step hides behind the previous tile's epilogue instead of standing in front of every tile.
-// Few rows (the count is read on the device): when the C tiles of a launch would not even give every compute unit
-// one, the launch is cut into the smaller CS tiles instead (same columns, half the rows, so twice as many
-// workgroups have work) and each tile runs its main loop with a deeper ring of its own, because a workgroup that has
-// its compute unit to itself spends a step waiting for that step's loads.  An output element is accumulated over k
-// in the same order by either tiling, so the bits of a row do not depend on how many rows are computed with it.
-// Launch bounds: every tiling counts on two workgroups to a compute unit, which is four wavefronts to a SIMD and at most
-// 128 registers (93 are used, with the bound and without).
-template <class C, class CS>
-__global__ __launch_bounds__(C::THREADS, 4) void gemm_bf16_dma_kernel(GemmArgs g, int tiles_n) {
-  static_assert(C::THREADS == CS::THREADS && C::BN == CS::BN, "the two tilings share the launch shape and the column tiles");
+// Time of `tiles` tiles of nk steps (units of 10 ns): whole rounds of 512 tiles, two to a compute unit, and what is left over,
+// one to a compute unit if that many are enough.  A round is a tile's fixed part and its steps; both are fits to the
+// layers of 256-, 768- and 1024-wide blocks at 64 to 32,768 rows, each tiling forced in turn, weights from HBM.  The rule
+// takes the fastest tiling or one within 5 % of it at these sizes: at 768 columns and K = 3072, 128 x 192 / 128 x 128 / 64 x
+// 128 / 64 x 64 / 32 x 64 tiles take 116 / 135 / 166 / 208 / - us for 24,576 rows, 65 / 52 / 72 / 87 / - for 9984, 45 / 39 /
+// 36 / 37 / 47 for 4096, 43 / 37 / 20 / 24 / 25 for 2048, 43 / 37 / 19 / 13 / 17 for 788, 35 / 27 / 17 / 11 / 10 for 256.
+struct GemmCost { int both_fixed, both_step, alone_fixed, alone_step; };
+__device__ __forceinline__ int gemm_cost(int tiles, int nk, GemmCost c) {
+  const int rest = tiles % kGemmGrid;
+  return (tiles / kGemmGrid) * (c.both_fixed + nk * c.both_step) +
+         (rest == 0 ? 0 : rest <= kGemmGrid / 2 ? c.alone_fixed + nk * c.alone_step : c.both_fixed + nk * c.both_step);
+}
+
+template <int EPI>
+__global__ __launch_bounds__(256, 2) void gemm_bf16_dma_kernel(GemmArgs g) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds_dyn[];
   const int n_seq = g.count ? min(*g.count, g.max_seqs) : g.max_seqs;
   const int M = n_seq * g.S;
-  const int tiles_m = (M + C::BM - 1) / C::BM;
-  const int total = tiles_m * tiles_n;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  if (total <= kGemmSmallTiles) {
-    const int few_n = (g.N + GemmFew::BN - 1) / GemmFew::BN, few = ((M + GemmFew::BM - 1) / GemmFew::BM) * few_n;
-    if (few <= kGemmFewTiles) {
-      gemm_few_tiles(g, M, few, few_n, lds_dyn);
-      return;
-    }
-    const int total_s = ((M + CS::BM - 1) / CS::BM) * tiles_n;
-    const uint16_t* A = (const uint16_t*)g.A;
-    const uint16_t* W = (const uint16_t*)g.W;
-    for (int tile = blockIdx.x; tile < total_s; tile += gridDim.x) {
-      const int m0 = (tile / tiles_n) * CS::BM, n0 = (tile % tiles_n) * CS::BN;
-      const uint16_t* a_ptr[CS::A_INSTR];
-      const uint16_t* b_ptr[CS::B_INSTR];
-#pragma unroll
-      for (int j = 0; j < CS::A_INSTR; ++j) {
-        const int tr = CS::load_row(j, wave, lane);
-        const int r = min(m0 + tr, M - 1);
-        a_ptr[j] = A + map_row(g.a_rows, r, g.S) * g.lda + CS::load_chunk(tr, lane) * 8;
-      }
-#pragma unroll
-      for (int j = 0; j < CS::B_INSTR; ++j) {
-        const int tr = CS::load_row(j, wave, lane);
-        const int r = min(n0 + tr, g.N - 1);
-        b_ptr[j] = W + (size_t)r * g.K + CS::load_chunk(tr, lane) * 8;
-      }
-      f32x16_t acc[CS::FM][CS::FN];
-#pragma unroll
-      for (int i = 0; i < CS::FM; ++i)
-#pragma unroll
-        for (int j = 0; j < CS::FN; ++j)
-#pragma unroll
-          for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-      mma_block_dma<CS>(a_ptr, b_ptr, g.K, lds_dyn, acc);
-      // every stage is free after the main loop: the staging of the epilogue takes the first one
-      gemm_epilogue_wave16<CS>(g, acc, m0, n0, M, reinterpret_cast<float*>(lds_dyn), false);
-      dma::barrier();             // ... and is read out before the next tile's first loads land there
-    }
-    return;
+  if (M <= 0) return;
+  const int nk = g.K / 64;
+  const int n64 = (g.N + 63) / 64, n128 = (n64 + 1) / 2, n192 = (n64 + 2) / 3;
+  const int m128 = (M + 127) / 128, m64 = (M + 63) / 64, m32 = (M + 31) / 32;
+  constexpr int act = EPI == kEpiGeluErf || EPI == kEpiGeluTanh ? 200 : 0;    // alone, nothing covers a large tile's epilogue
+  constexpr GemmCost big = {860, 117, 600 + act, 82}, mid = {600, 89, 150 + act, 75}, low = {350, 66, 260, 39},
+                     tiny = {100, 44, 150, 23}, few = {100, 30, 130, 19};
+  int path = 0;
+  const int tiles = m128 * n192;
+  if (nk < 2 || tiles <= 4 * kGemmGrid) {
+    int best = nk < 2 ? 0x7FFFFFFF : gemm_cost(tiles, nk, big);            // the ring starts with two steps
+    auto offer = [&](int p, int t, GemmCost c) {
+      const int cost = gemm_cost(t, nk, c);
+      if (cost < best) { best = cost; path = p; }
+    };
+    if (nk >= 2) offer(1, m128 * n128, mid);
+    offer(2, m64 * n128, low);
+    offer(3, m64 * n64, tiny);
+    offer(4, m32 * n64, few);
+  } else {
+    path = n192 * (big.both_fixed + nk * big.both_step) > n128 * (mid.both_fixed + nk * mid.both_step) ? 1 : 0;
   }
-  // Workgroups are dealt round-robin to the 8 XCDs, each with its own L2.  With xcd_chunks set, XCD x
-  // walks the x-th eighth of the tile list, so the operand panels of neighbouring tiles are fetched into one L2
-  // only and shared there; otherwise workgroups stride over the tile list.  gridDim.x % 8 == 0 when xcd_chunks.
-  // xcd_chunks == 1: the list is row-major (the column tiles of a row block are adjacent: narrow outputs);
-  // xcd_chunks == 2: grouped order, the list runs down 8 row blocks before it moves one column tile on, so the 64
-  // tiles that an XCD's workgroups hold at one time are 8 row blocks x 8 column tiles: 16 operand panels (3 MB).
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, slots = gridDim.x >> 3;
-  const int per_xcd = (total + 7) >> 3;
-  const int n_it = g.xcd_chunks ? per_xcd : total;
-  const int it_step = g.xcd_chunks ? slots : (int)gridDim.x;
-  const uint16_t* A = (const uint16_t*)g.A;
-  const uint16_t* W = (const uint16_t*)g.W;
-  const uint16_t* a_ptr[C::A_INSTR];
-  const uint16_t* b_ptr[C::B_INSTR];
-  int m0 = 0, n0 = 0;
-  // tile of list position `it` (negative: none), and this lane's load addresses for it
-  auto locate = [&](int it) -> bool {
-    if (it >= n_it) return false;
-    const int tile = g.xcd_chunks ? xcd * per_xcd + it : it;
-    if (tile >= total) return false;
-    int tile_m = tile / tiles_n, tile_n = tile % tiles_n;
-    if (g.xcd_chunks == 2) {
-      const int group = tile / (8 * tiles_n), in_group = tile % (8 * tiles_n);
-      const int rows_in_group = min(8, tiles_m - group * 8);
-      tile_m = group * 8 + in_group % rows_in_group;
-      tile_n = in_group / rows_in_group;
-    }
-    m0 = tile_m * C::BM;
-    n0 = tile_n * C::BN;
-#pragma unroll
-    for (int j = 0; j < C::A_INSTR; ++j) {
-      const int tr = C::load_row(j, wave, lane);
-      const int r = min(m0 + tr, M - 1);
-      a_ptr[j] = A + map_row(g.a_rows, r, g.S) * g.lda + C::load_chunk(tr, lane) * 8;
-    }
-#pragma unroll
-    for (int j = 0; j < C::B_INSTR; ++j) {
-      const int tr = C::load_row(j, wave, lane);
-      const int r = min(n0 + tr, g.N - 1);
-      b_ptr[j] = W + (size_t)r * g.K + C::load_chunk(tr, lane) * 8;
-    }
-    return true;
-  };
-  int it = g.xcd_chunks ? slot : (int)blockIdx.x;
-  if (!locate(it)) return;
-  const int nk = g.K / C::BK;
-  int ring = 0;
-  dma_issue<C>(a_ptr, b_ptr, 0, 0, lds_dyn);
-  LLMC_WAIT_VM(0);
-  while (true) {
-    f32x16_t acc[C::FM][C::FN];
-#pragma unroll
-    for (int i = 0; i < C::FM; ++i)
-#pragma unroll
-      for (int j = 0; j < C::FN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    mma_block_dma_ring<C>(a_ptr, b_ptr, g.K, lds_dyn, acc, ring);
-    const int cur_m0 = m0, cur_n0 = n0;
-    const int last_stage = (ring + nk - 1) & 1;
-    ring += nk;
-    it += it_step;
-    const bool more = locate(it);                       // uniform over the workgroup
-    if (more) dma_issue<C>(a_ptr, b_ptr, 0, ring & 1, lds_dyn);
-    gemm_epilogue_wave16<C>(g, acc, cur_m0, cur_n0, M, reinterpret_cast<float*>(lds_dyn + last_stage * C::STAGE_ELEMS), more);
-    if (!more) break;
-  }
+  if (path == 0) gemm_ring_tiles<GemmBig, EPI>(g, M, lds_dyn);
+  else if (path == 1) gemm_ring_tiles<GemmMid, EPI>(g, M, lds_dyn);
+  else if (path == 2) gemm_step_tiles<GemmLow, EPI>(g, M, lds_dyn);
+  else if (path == 3) gemm_step_tiles<GemmTiny, EPI>(g, M, lds_dyn);
+  else gemm_step_tiles<GemmFew, EPI>(g, M, lds_dyn);
 }
 
 }  // namespace llmc

@@ -17,57 +17,33 @@
 
 namespace llmc {
 
-typedef MmaCfg<128, 128, 32, 2, 2> GemmCfg;
-
 // Launches are sized for the worst case (every sequence a miss) but capped: workgroups walk
 // their tiles / rows with a grid stride and read the real count on the device, so a layer
 // with few or no misses costs a small, fixed number of idle workgroups.
 constexpr int kMaxGrid = 512;
 
-// 128 x 128 block, 8 wavefronts (2 x 4), two 64-column stages filled by direct-to-LDS loads: 68 KiB of LDS,
-// so two workgroups share a compute unit and one's epilogue overlaps the other's main loop
-typedef DmaCfg<128, 128, 2, 4, 2> GemmDmaCfg;
-// with few rows: 64 x 128 blocks, three stages (72 KiB, still two workgroups per compute unit)
-typedef DmaCfg<64, 128, 2, 4, 3> GemmDmaSmallCfg;
-
-static llmc_status_t launch_gemm(const GemmArgs& g, int dtype, hipStream_t st) {
-  if (dtype == LLMC_BF16) {
-    if (g.K % 64 == 0) {
-      using C = GemmDmaCfg;
-      using CS = GemmDmaSmallCfg;
-      static std::atomic<bool> lds_set[64];
-      const auto kernel = gemm_bf16_dma_kernel<C, CS>;
-      const size_t lds_bytes = gemm_dma_smem_bytes<C, CS>();
-      LLMC_TRY(ensure_dynamic_lds((const void*)kernel, lds_bytes, lds_set));
-      const int tiles_n = (g.N + C::BN - 1) / C::BN;
-      // the grid covers the smaller tilings too, which the kernel takes when the rows it finds on the device are few
-      static_assert(GemmFew::LDS_BYTES <= gemm_dma_smem_bytes<C, CS>(), "the stages of every tiling fit the launch");
-      const int tiles_m = (g.max_seqs * g.S + CS::BM - 1) / CS::BM;
-      const int64_t few = (int64_t)((g.max_seqs * g.S + GemmFew::BM - 1) / GemmFew::BM) * ((g.N + GemmFew::BN - 1) / GemmFew::BN);
-      const int64_t tiles = std::max((int64_t)tiles_m * tiles_n, few);
-      GemmArgs a = g;
-      // Every XCD walks its own eighth of the tile list, wide outputs in grouped order; where the column tiles divide by
-      // eight, plain striding gives each XCD its own eighth of the COLUMNS instead, so the L2 keeps its weights and only
-      // the rows stream (4096 rows, K = 1024: 3072 columns 38.8 -> 33.2 us, 4096 columns 49.6 -> 45.8; 24576 rows of
-      // K = 768 the same either way; 18 column tiles strided 120 us against 114).  The four layers of a block, strided /
-      // grouped: 146 / 153 us at 4096 rows of 1024 and 501 / 513 of 2048, 1075 / 1058 and 3768 / 3726 at 32768 rows,
-      // equal within the noise for widths of 256 and 512 and for fewer rows.
-      a.xcd_chunks = tiles_n <= 8 ? 1 : tiles_n % 8 == 0 ? 0 : 2;
-      ProfScope ps_("gemm_bf16_kernel", st);
-      LLMC_KERNEL_GGL(kernel, dim3((unsigned)std::min<int64_t>((tiles + 7) & ~7ll, kMaxGrid)), dim3(C::THREADS), lds_bytes, st, a,
-                      tiles_n);
-    } else {
-      const int tiles_n = (g.N + GemmCfg::BN - 1) / GemmCfg::BN;
-      const int tiles_m = (g.max_seqs * g.S + GemmCfg::BM - 1) / GemmCfg::BM;
-      ProfScope ps_("gemm_bf16_kernel", st);
-      LLMC_KERNEL_GGL(gemm_bf16_kernel<GemmCfg>, dim3(std::min(tiles_m * tiles_n, kMaxGrid)), dim3(GemmCfg::THREADS),
-                         0, st, g, tiles_n);
-    }
-  } else {
-    return launch_gemm_f32(g, st);
-  }
+template <int EPI>
+static llmc_status_t launch_gemm_bf16(const GemmArgs& args, hipStream_t st) {
+  GemmArgs g = args;
+  g.s_magic = row_magic(g.S);
+  static std::atomic<bool> lds_set[64];
+  const auto kernel = gemm_bf16_dma_kernel<EPI>;
+  LLMC_TRY(ensure_dynamic_lds((const void*)kernel, kGemmLdsBytes, lds_set));
+  // as many workgroups as the smallest tiles could use if every sequence were computed; the kernel reads the count
+  const int64_t tiles = (((int64_t)g.max_seqs * g.S + GemmFew::BM - 1) / GemmFew::BM) * ((g.N + GemmFew::BN - 1) / GemmFew::BN);
+  ProfScope ps_("gemm_bf16_kernel", st);
+  LLMC_KERNEL_GGL(kernel, dim3((unsigned)std::min<int64_t>((tiles + 7) & ~7ll, kGemmGrid)), dim3(256), kGemmLdsBytes, st, g);
   LLMC_LAUNCH_CHECK("gemm");
   return LLMC_OK;
+}
+
+// K a multiple of 64, N of 8; an activation and a residual exclude each other
+static llmc_status_t launch_gemm(const GemmArgs& g, int dtype, hipStream_t st) {
+  if (dtype != LLMC_BF16) return launch_gemm_f32(g, st);
+  if (g.act == 1) return launch_gemm_bf16<kEpiGeluErf>(g, st);
+  if (g.act == 2) return launch_gemm_bf16<kEpiGeluTanh>(g, st);
+  if (g.resid) return launch_gemm_bf16<kEpiResidual>(g, st);
+  return launch_gemm_bf16<kEpiPlain>(g, st);
 }
 
 // ---- LayerNorm: one wavefront per token, two-pass statistics in fp32 -----------------------------

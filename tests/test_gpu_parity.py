@@ -1939,6 +1939,18 @@ def test_bf16_layer_tilings(L, arch, d, dff, S, B):
 
 
 @pytest.mark.parametrize("d,dff,S,B", [
+    (128, 320, 131, 130),    # 17,030 tokens, two steps of k (as many as the ring starts with), ragged column tiles
+    (448, 704, 97, 90),      # 8730 tokens, 26 in the last row of tiles; 1344, 448 and 704 columns in tiles of 192 and 128
+    (576, 1152, 67, 61),     # 4087 tokens: 64 x 128 and 64 x 64 tiles among the larger ones, nine and 18 steps
+    (1024, 4096, 128, 33),   # columns that divide by eight tiles, more tiles than workgroups
+])
+@pytest.mark.parametrize("arch", [0, 1])
+def test_bf16_layer_tilings_of_many_rows(L, arch, d, dff, S, B):
+    """The bf16 block on the tilings for many rows against the oracle, and the same bits for the last sequence alone."""
+    test_bf16_layer_tilings(L, arch, d, dff, S, B)
+
+
+@pytest.mark.parametrize("d,dff,S,B", [
     (64, 64, 1, 1),          # one token, one column tile
     (192, 320, 33, 3),       # 99 tokens: ragged against 32 and 64 rows, widths that are odd multiples of 64
     (128, 64, 145, 2),       # attention: two query blocks and a third of 17, five key tiles, the last with 17 keys

@@ -55,6 +55,8 @@ struct GemmArgs {
   const int32_t* count;            // device: number of sequences; null = max_seqs
   int max_seqs;
   uint64_t s_magic;                // row_magic(S), of the bf16 form
+  const void* ahead[3];            // bf16 form: weights of the launches that follow (or null) ...
+  uint32_t ahead_bytes[3];         // ... and their sizes, multiples of 16
   const int32_t* a_rows;           // sequence list applied to A rows, or null
   const int32_t* r_rows;           // ... to residual rows
   const int32_t* o_rows;           // ... to output rows
@@ -562,6 +564,23 @@ __device__ __forceinline__ int gemm_cost(int tiles, int nk, GemmCost c) {
          (rest == 0 ? 0 : rest <= kGemmGrid / 2 ? c.alone_fixed + nk * c.alone_step : c.both_fixed + nk * c.both_step);
 }
 
+// What a workgroup without a tile reads of the weights that follow: four rounds of 16 KiB, about as long as the tiles of a
+// small launch take.  Without the limit the 44 workgroups that 788 rows of a 768-wide block leave over read for 16 us beside
+// tiles of 8.
+constexpr uint32_t kGemmTouchBytes = 64 * 1024;
+// Read `bytes` of `p` and drop them: workgroup `i` of `n`, 16 KiB at a time.
+__device__ __forceinline__ void gemm_touch(const void* p, uint32_t bytes, int i, int n) {
+  const uint4* v = reinterpret_cast<const uint4*>(p);
+  const uint32_t count = bytes / 16;
+  for (uint32_t at = i * 1024 + threadIdx.x; at < count; at += n * 1024) {
+    uint4 x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) x[u] = v[min(at + u * 256, count - 1)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) asm volatile("" ::"v"(x[u].x), "v"(x[u].y), "v"(x[u].z), "v"(x[u].w));
+  }
+}
+
 template <int EPI>
 __global__ __launch_bounds__(256, 2) void gemm_bf16_dma_kernel(GemmArgs g) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds_dyn[];
@@ -574,18 +593,28 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_dma_kernel(GemmArgs g) {
   constexpr int act = EPI == kEpiGeluErf || EPI == kEpiGeluTanh ? 200 : 0;    // alone, nothing covers a large tile's epilogue
   constexpr GemmCost big = {860, 117, 600 + act, 82}, mid = {600, 89, 150 + act, 75}, low = {350, 66, 260, 39},
                      tiny = {100, 44, 150, 23}, few = {100, 30, 130, 19};
-  int path = 0;
-  const int tiles = m128 * n192;
+  int path = 0, tiles = m128 * n192;
   if (nk < 2 || tiles <= 4 * kGemmGrid) {
     int best = nk < 2 ? 0x7FFFFFFF : gemm_cost(tiles, nk, big);            // the ring starts with two steps
     auto offer = [&](int p, int t, GemmCost c) {
       const int cost = gemm_cost(t, nk, c);
-      if (cost < best) { best = cost; path = p; }
+      if (cost < best) { best = cost; path = p; tiles = t; }
     };
     if (nk >= 2) offer(1, m128 * n128, mid);
     offer(2, m64 * n128, low);
     offer(3, m64 * n64, tiny);
     offer(4, m32 * n64, few);
+    const int busy = (tiles + 7) & ~7;                   // workgroups beyond have no tile, in any order of the tiles
+    if ((int)blockIdx.x >= busy) {
+      const int n = gridDim.x - busy;
+      uint32_t left = (uint32_t)n * kGemmTouchBytes;
+      for (int i = 0; i < 3; ++i) {
+        const uint32_t bytes = min(g.ahead_bytes[i], left);
+        gemm_touch(g.ahead[i], bytes, blockIdx.x - busy, n);
+        left -= bytes;
+      }
+      return;
+    }
   } else {
     path = n192 * (big.both_fixed + nk * big.both_step) > n128 * (mid.both_fixed + nk * mid.both_step) ? 1 : 0;
   }

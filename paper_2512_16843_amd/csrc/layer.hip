@@ -31,8 +31,9 @@ static llmc_status_t launch_gemm_bf16(const GemmArgs& args, hipStream_t st) {
   LLMC_TRY(ensure_dynamic_lds((const void*)kernel, kGemmLdsBytes, lds_set));
   // as many workgroups as the smallest tiles could use if every sequence were computed; the kernel reads the count
   const int64_t tiles = (((int64_t)g.max_seqs * g.S + GemmFew::BM - 1) / GemmFew::BM) * ((g.N + GemmFew::BN - 1) / GemmFew::BN);
+  const int64_t grid = g.ahead[0] ? kGemmGrid : std::min<int64_t>((tiles + 7) & ~7ll, kGemmGrid);
   ProfScope ps_("gemm_bf16_kernel", st);
-  LLMC_KERNEL_GGL(kernel, dim3((unsigned)std::min<int64_t>((tiles + 7) & ~7ll, kGemmGrid)), dim3(256), kGemmLdsBytes, st, g);
+  LLMC_KERNEL_GGL(kernel, dim3((unsigned)grid), dim3(256), kGemmLdsBytes, st, g);
   LLMC_LAUNCH_CHECK("gemm");
   return LLMC_OK;
 }
@@ -297,8 +298,24 @@ static llmc_status_t layer_t(const llmc_layer_desc_t* L, const void* h_in, void*
     a.resid = resid; a.ldr = N; a.r_rows = r_rows; a.out = out; a.ldo = N; a.o_rows = o_rows;
     return launch_gemm(a, L->dtype, st);
   };
+  // The first product's workgroups that find no tile read the weights of the other three: with few rows those layers are
+  // bound by the latency of their weights, which is that of the memory-side cache then and not that of HBM.  (Stacks of 12
+  // 768-wide layers whose weights come from HBM, microseconds: one sequence of 128 tokens 1059 -> 1015, prefix keys with 2
+  // of 16 sequences computed 2930 -> 2842.)  Nothing is read where no row is computed, or every workgroup has a tile.
+  GemmArgs with_ahead = g;
+  const void* const rest[3] = {L->d_wo, L->d_w1, L->d_w2};
+  const size_t rest_bytes[3] = {(size_t)d * d * e, (size_t)d * dff * e, (size_t)d * dff * e};
+  for (int i = 0; i < 3; ++i)
+    if (rest_bytes[i] < (1ull << 28)) { with_ahead.ahead[i] = rest[i]; with_ahead.ahead_bytes[i] = (uint32_t)rest_bytes[i]; }
+  auto gemm_qkv = [&](const void* A, const int32_t* a_rows) {
+    const GemmArgs plain = g;
+    g = with_ahead;
+    const llmc_status_t s = gemm(A, d, a_rows, L->d_wqkv, L->d_bqkv, 3 * d, d, 0, nullptr, nullptr, qkv, nullptr);
+    g = plain;
+    return s;
+  };
   if (L->arch == 0) {
-    LLMC_TRY(gemm(h_in, d, rows, L->d_wqkv, L->d_bqkv, 3 * d, d, 0, nullptr, nullptr, qkv, nullptr));
+    LLMC_TRY(gemm_qkv(h_in, rows));
     LLMC_TRY(launch_attention<T>(qkv, ctx, S, d, L->n_heads, false, count, B, st));
     LLMC_TRY(gemm(ctx, d, nullptr, L->d_wo, L->d_bo, d, d, 0, h_in, rows, t0, nullptr));
     LLMC_TRY(launch_ln<T>(t0, nullptr, t1, nullptr, L->d_ln1_g, L->d_ln1_b, L->ln_eps, d, S, count, B, st));
@@ -311,7 +328,7 @@ static llmc_status_t layer_t(const llmc_layer_desc_t* L, const void* h_in, void*
       LLMC_TRY(launch_ln<T>(t0, nullptr, h_out, rows, L->d_ln2_g, L->d_ln2_b, L->ln_eps, d, S, count, B, st));
   } else {
     LLMC_TRY(launch_ln<T>(h_in, rows, t1, nullptr, L->d_ln1_g, L->d_ln1_b, L->ln_eps, d, S, count, B, st));
-    LLMC_TRY(gemm(t1, d, nullptr, L->d_wqkv, L->d_bqkv, 3 * d, d, 0, nullptr, nullptr, qkv, nullptr));
+    LLMC_TRY(gemm_qkv(t1, nullptr));
     LLMC_TRY(launch_attention<T>(qkv, ctx, S, d, L->n_heads, true, count, B, st));
     LLMC_TRY(gemm(ctx, d, nullptr, L->d_wo, L->d_bo, d, d, 0, h_in, rows, t0, nullptr));
     LLMC_TRY(launch_ln<T>(t0, nullptr, t1, nullptr, L->d_ln2_g, L->d_ln2_b, L->ln_eps, d, S, count, B, st));

@@ -120,6 +120,30 @@ __device__ __forceinline__ float wave_sum(float v) {
   v += __uint_as_float(butterfly_u32<1>(__float_as_uint(v)));
   return v;
 }
+// N of them side by side
+template <int N>
+__device__ __forceinline__ void wave_sums(float (&v)[N]) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    uint32_t a, b;
+    butterfly_pair_u32<32>(__float_as_uint(v[i]), a, b);
+    v[i] = __uint_as_float(a) + __uint_as_float(b);
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    uint32_t a, b;
+    butterfly_pair_u32<16>(__float_as_uint(v[i]), a, b);
+    v[i] = __uint_as_float(a) + __uint_as_float(b);
+  }
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] += __uint_as_float(butterfly_u32<8>(__float_as_uint(v[i])));
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] += __uint_as_float(butterfly_u32<4>(__float_as_uint(v[i])));
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] += __uint_as_float(butterfly_u32<2>(__float_as_uint(v[i])));
+#pragma unroll
+  for (int i = 0; i < N; ++i) v[i] += __uint_as_float(butterfly_u32<1>(__float_as_uint(v[i])));
+}
 template <int O>
 __device__ __forceinline__ double butterfly_add(double v) {
   const uint64_t u = __builtin_bit_cast(uint64_t, v);

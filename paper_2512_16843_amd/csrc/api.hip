@@ -684,8 +684,8 @@ llmc_status_t llmc_layer_forward_gated(const llmc_layer_desc_t* layer, llmc_bank
   if ((flags & LLMC_REVALIDATE) && bank->desc.reval_every > 0)
     LLMC_TRY(launch_divergence(bank, d_h_out, idx, miss_rows, counters, B, st));
   if (flags & LLMC_INSERT_ON_MISS)
-    LLMC_TRY(launch_bank_insert(bank, q, qinv, d_h_out, miss_rows, counters + LLMC_CNT_MISS, B, tick, slots, counters,
-                                st));
+    LLMC_TRY(launch_bank_insert(bank, q, qinv, d_h_out, miss_rows, counters + LLMC_CNT_MISS, B, tick, slots, counters, st,
+                                pooled_valid_out && layer_pools_outputs(layer) ? (const float*)ws_fp : nullptr));
   if (flags & LLMC_DEDUP)
     LLMC_TRY(launch_dedup_finish(bank, d_h_out, B, slots, idx, sim, hit, counters, flags, ws_dedup, st));
   return LLMC_OK;

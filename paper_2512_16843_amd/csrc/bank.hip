@@ -327,7 +327,7 @@ llmc_status_t launch_bank_refresh(llmc_bank* bank, hipStream_t st) {
 
 llmc_status_t launch_bank_insert(llmc_bank* bank, const void* d_fp, const float* d_inv, const void* d_act,
                                  const int32_t* d_rows, const int32_t* d_m, int m_max, uint64_t tick,
-                                 int32_t* d_slots_out, int32_t* d_counters, hipStream_t st) {
+                                 int32_t* d_slots_out, int32_t* d_counters, hipStream_t st, const float* chunk_sums) {
   const llmc_bank_desc_t& D = bank->desc;
   LLMC_TRY(launch_bank_advance(bank, tick, st));
   { ProfScope ps_("select_kernel", st);
@@ -349,10 +349,15 @@ llmc_status_t launch_bank_insert(llmc_bank* bank, const void* d_fp, const float*
                      D.d_last_used, D.d_hits, D.d_valid, bank->d_binv_eff, words_per_key, vec_per_seq, tick, d_counters,
                      D.key_bits); }
   LLMC_LAUNCH_CHECK("insert_kernel");
-  // the token mean of every stored output, kept beside it (dropped rows have slot -1 and are skipped)
+  // The token mean of every stored output, kept beside it (dropped rows have slot -1 and are skipped), and the key under
+  // which the next layer will look it up.
+  if (D.d_act_pool && chunk_sums) {
+    LLMC_TRY(launch_keep_stored(chunk_sums, m_max, D.S, D.d, D.dtype, d_rows, d_m, d_slots_out, D.d_act_pool,
+                                D.d_next_fp ? D.d_next_proj : nullptr, D.d_next_bias, D.next_k, D.d_next_fp, D.d_next_inv, st));
+    return rebuild_lsh_index(bank, st, d_m);
+  }
   if (D.d_act_pool)
     LLMC_TRY(launch_pool_rows(d_act, m_max, D.S, D.d, D.dtype, d_rows, d_m, d_slots_out, D.d_act_pool, st));
-  // ... and the key under which the next layer will look it up
   if (D.d_next_fp)
     LLMC_TRY(launch_project_rows(D.d_act_pool, m_max, D.d, D.dtype, D.d_next_proj, D.d_next_bias, D.next_k, d_slots_out,
                                  d_m, D.d_next_fp, D.d_next_inv, st));

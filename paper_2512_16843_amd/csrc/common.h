@@ -260,6 +260,10 @@ llmc_status_t launch_pool_means(const void* d_h, int B, int S, int d, int dtype,
                                 int ld_out, hipStream_t st);
 llmc_status_t launch_pool_rows(const void* d_h, int n_max, int S, int d, int dtype, const int32_t* d_rows,
                                const int32_t* d_count, const int32_t* d_dst, float* d_out, hipStream_t st);
+// means and next-layer keys of sequences just stored, from chunk sums [.., ceil(S / 64), d] of theirs by sequence
+llmc_status_t launch_keep_stored(const float* partial, int n_max, int S, int d, int dtype, const int32_t* d_rows,
+                                 const int32_t* d_count, const int32_t* d_dst, float* d_means, const void* d_proj,
+                                 const float* d_bias, int k, void* d_fp, float* d_inv, hipStream_t st);
 llmc_status_t launch_fingerprint_bits(const void* d_h, int B, int S, int d, int dtype, const void* d_proj,
                                       const float* d_bias, int k, uint32_t* d_bits, void* ws, hipStream_t st,
                                       const float* pooled_in = nullptr, const uint8_t* pooled_valid = nullptr,
@@ -321,7 +325,8 @@ llmc_status_t launch_transpose(const void* in, void* out, int r, int d, int e, h
 llmc_status_t launch_bank_advance(llmc_bank* bank, uint64_t tick, hipStream_t st);
 llmc_status_t launch_bank_insert(llmc_bank* bank, const void* d_fp, const float* d_inv, const void* d_act,
                                  const int32_t* d_rows, const int32_t* d_m, int m_max, uint64_t tick,
-                                 int32_t* d_slots_out, int32_t* d_counters, hipStream_t st);
+                                 int32_t* d_slots_out, int32_t* d_counters, hipStream_t st,
+                                 const float* chunk_sums = nullptr);   // of the listed rows, by row, if they are at hand
 llmc_status_t launch_bank_evict(llmc_bank* bank, const int32_t* d_m, int m_max, int32_t* d_victims,
                                 hipStream_t st);
 
@@ -340,6 +345,8 @@ size_t layer_ws_bytes(const llmc_layer_desc_t* L, int B, int S);
 llmc_status_t launch_linear(const void* A, int lda, const int32_t* a_rows, const void* W, const void* bias, int N, int K,
                             void* out, int ldo, const int32_t* o_rows, int S, const int32_t* count, int max_seqs,
                             int dtype, hipStream_t st);
+// whether launch_layer honours pool_partial for this block
+bool layer_pools_outputs(const llmc_layer_desc_t* L);
 // pool_partial / pooled_flags (both or neither): the block's last LayerNorm also leaves the chunk sums of its
 // outputs in the fingerprint's partials buffer and sets pooled_flags[row] = 2 (post-LayerNorm blocks whose rows fit)
 // bf16 softmax attention on the matrix cores (head size 64): qkv [T, 3d] -> ctx [T, d]; sequences beyond *count skipped

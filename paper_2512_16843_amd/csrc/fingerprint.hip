@@ -148,13 +148,17 @@ __global__ __launch_bounds__(1024) void project_kernel(const float* __restrict__
                                                        const int32_t* __restrict__ row_map,
                                                        const int32_t* __restrict__ count,
                                                        const T* __restrict__ h_inline, int G, int R,
-                                                       const int32_t* __restrict__ key_index) {
+                                                       const int32_t* __restrict__ key_index,
+                                                       const int32_t* __restrict__ part_rows,
+                                                       float* __restrict__ mean_out) {
   // With h_inline (needs blockDim >= G * R and LDS for R * d more floats): a row whose mean is not supplied is
   // pooled here, by this workgroup, with pool_sequence -- no partials, no separate pooling launch.
   // Entry e = blockIdx.x works on row b = row_map[e] (or e) of the outputs.  Sources of the token mean of row b:
   // pooled_in[b] if pooled_in is given and either there are no flags (means kept elsewhere, e.g. beside a bank's
   // values, possibly through row_map) or pooled_valid[b] is set; else the chunk partials of entry e.  If key_in is given and pooled_valid[b], the finished key
   // itself was supplied: it is copied and nothing is computed.
+  // With part_rows (and row_map): the chunk sums of entry e are those of sequence part_rows[e], and the mean formed from
+  // them is kept in mean_out[b].
   extern __shared__ float sm[];   // p[d] | v[parts][k]
   float* p = sm;
   float* vpart = sm + d;
@@ -191,7 +195,7 @@ __global__ __launch_bounds__(1024) void project_kernel(const float* __restrict__
     }
   } else
   for (int i = threadIdx.x; i < d; i += nthreads) {
-    const float* src = partial + (size_t)entry * n_chunks * d + i;
+    const float* src = partial + (size_t)(part_rows ? part_rows[entry] : entry) * n_chunks * d + i;
     float s = 0.f;
     // eight chunk partials in flight; added in ascending chunk order
     constexpr int UC = 8;
@@ -212,6 +216,7 @@ __global__ __launch_bounds__(1024) void project_kernel(const float* __restrict__
         if (c + u < n_chunks) s += x[u];
     }
     p[i] = s * inv_S;
+    if (mean_out) mean_out[(size_t)b * d + i] = p[i];
   }
   __syncthreads();
   {
@@ -375,7 +380,8 @@ static llmc_status_t fingerprint_t(const T* h, int B, int S, int d, const T* P, 
     LLMC_KERNEL_GGL(project_kernel<T>, dim3(B), dim3(threads),
                        (size_t)(d + parts * k + (inline_pool ? R * d : 0)) * sizeof(float), st, partial, n_chunks, S, d, P,
                        bias, k, parts, fp, inv, bits, pooled_in, pooled_valid, key_in, key_inv_in, (const int32_t*)nullptr,
-                       (const int32_t*)nullptr, inline_pool ? h : (const T*)nullptr, G, R, key_index);
+                       (const int32_t*)nullptr, inline_pool ? h : (const T*)nullptr, G, R, key_index,
+                       (const int32_t*)nullptr, (float*)nullptr);
   }
   LLMC_LAUNCH_CHECK("project_kernel");
   return LLMC_OK;
@@ -399,11 +405,17 @@ llmc_status_t launch_fingerprint(const void* d_h, const int32_t*, int B, int S, 
 // the bits the fingerprint uses) and writes out[b * ld_out ..] [d]
 // grid (B, ceil(d / 256)): a thread owns one column; sixteen chunk sums are in flight (one at a time, 16 sequences of 16
 // chunks took 12.6 us, now 4.1, where an empty launch is timed at 4.0)
+// With rows, dst and count: entry e < *count takes the chunk sums of sequence rows[e] to out[dst[e]], none where negative.
 __global__ __launch_bounds__(256) void mean_from_partials_kernel(const float* __restrict__ partial, int n_chunks, int d,
-                                                                 float inv_S, float* __restrict__ out, int ld_out) {
-  const int b = blockIdx.x, i = blockIdx.y * 256 + threadIdx.x;
-  if (i >= d) return;
-  const float* src = partial + (size_t)b * n_chunks * d + i;
+                                                                 float inv_S, float* __restrict__ out, int ld_out,
+                                                                 const int32_t* __restrict__ rows,
+                                                                 const int32_t* __restrict__ dst,
+                                                                 const int32_t* __restrict__ count) {
+  const int e = blockIdx.x, i = blockIdx.y * 256 + threadIdx.x;
+  if (i >= d || (count && e >= *count)) return;
+  const int b = dst ? dst[e] : e;
+  if (b < 0) return;
+  const float* src = partial + (size_t)(rows ? rows[e] : e) * n_chunks * d + i;
   float s = 0.f;
   for (int c = 0; c < n_chunks; c += 16) {
     float x[16];
@@ -428,7 +440,8 @@ static llmc_status_t pool_means_t(const T* h, int B, int S, int d, float* partia
                     (const int32_t*)nullptr); }
   LLMC_LAUNCH_CHECK("pool_kernel");
   { ProfScope ps_("mean_from_partials_kernel", st);
-    LLMC_KERNEL_GGL(mean_from_partials_kernel, dim3(B, (d + 255) / 256), dim3(256), 0, st, partial, n_chunks, d, 1.0f / (float)S, out, ld_out); }
+    LLMC_KERNEL_GGL(mean_from_partials_kernel, dim3(B, (d + 255) / 256), dim3(256), 0, st, partial, n_chunks, d, 1.0f / (float)S, out, ld_out,
+                    (const int32_t*)nullptr, (const int32_t*)nullptr, (const int32_t*)nullptr); }
   LLMC_LAUNCH_CHECK("mean_from_partials_kernel");
   return LLMC_OK;
 }
@@ -449,7 +462,7 @@ static llmc_status_t project_rows_t(const float* means, int n_max, int d, const 
   LLMC_KERNEL_GGL(project_kernel<T>, dim3(n_max), dim3(project_threads(cgs, parts, k)),
                      (size_t)(d + parts * k) * sizeof(float), st, (const float*)nullptr, 0, 1, d, P, bias, k, parts, fp, inv,
                      (uint32_t*)nullptr, means, (const uint8_t*)nullptr, (const T*)nullptr, (const float*)nullptr, rows,
-                     count, (const T*)nullptr, 0, 0, (const int32_t*)nullptr);
+                     count, (const T*)nullptr, 0, 0, (const int32_t*)nullptr, (const int32_t*)nullptr, (float*)nullptr);
   LLMC_LAUNCH_CHECK("project_kernel");
   return LLMC_OK;
 }
@@ -462,6 +475,43 @@ llmc_status_t launch_project_rows(const float* d_means, int n_max, int d, int dt
                                  st);
   return project_rows_t<bf16_t>(d_means, n_max, d, (const bf16_t*)d_proj, d_bias, k, d_rows, d_count, (bf16_t*)d_fp,
                                 d_inv, st);
+}
+
+// What a bank keeps beside the outputs it has just stored, from the chunk sums that the producing block left behind (the bits
+// that pooling the rows again would give): entry e < *count is sequence rows[e], stored in slot dst[e] (negative: dropped).
+// Its mean goes to means[slot]; with a map, its key under it to fp[slot], inv[slot].  32 sequences of 128 x 1024 bf16, 24
+// times a pass: pooling the rows again took 11.4 us each and the projection 13.4, the projection with the sums 13.6.
+template <typename T>
+static llmc_status_t keep_stored_t(const float* partial, int n_max, int S, int d, const int32_t* rows, const int32_t* count,
+                                   const int32_t* dst, float* means, const T* P, const float* bias, int k, T* fp, float* inv,
+                                   hipStream_t st) {
+  const int n_chunks = pool_chunks(S);
+  if (!P) {
+    ProfScope ps_("mean_from_partials_kernel", st);
+    LLMC_KERNEL_GGL(mean_from_partials_kernel, dim3(n_max, (d + 255) / 256), dim3(256), 0, st, partial, n_chunks, d,
+                    1.0f / (float)S, means, d, rows, dst, count);
+    LLMC_LAUNCH_CHECK("mean_from_partials_kernel");
+    return LLMC_OK;
+  }
+  const int cgs = k / 4;
+  const int parts = std::max(1, std::min(1024 / cgs, 16));
+  ProfScope ps_("project_kernel", st);
+  LLMC_KERNEL_GGL(project_kernel<T>, dim3(n_max), dim3(project_threads(cgs, parts, k)), (size_t)(d + parts * k) * sizeof(float),
+                  st, partial, n_chunks, S, d, P, bias, k, parts, fp, inv, (uint32_t*)nullptr, (const float*)nullptr,
+                  (const uint8_t*)nullptr, (const T*)nullptr, (const float*)nullptr, dst, count, (const T*)nullptr, 0, 0,
+                  (const int32_t*)nullptr, rows, means);
+  LLMC_LAUNCH_CHECK("project_kernel");
+  return LLMC_OK;
+}
+
+llmc_status_t launch_keep_stored(const float* partial, int n_max, int S, int d, int dtype, const int32_t* d_rows,
+                                 const int32_t* d_count, const int32_t* d_dst, float* d_means, const void* d_proj,
+                                 const float* d_bias, int k, void* d_fp, float* d_inv, hipStream_t st) {
+  if (dtype == LLMC_F32)
+    return keep_stored_t<float>(partial, n_max, S, d, d_rows, d_count, d_dst, d_means, (const float*)d_proj, d_bias, k,
+                                (float*)d_fp, d_inv, st);
+  return keep_stored_t<bf16_t>(partial, n_max, S, d, d_rows, d_count, d_dst, d_means, (const bf16_t*)d_proj, d_bias, k,
+                               (bf16_t*)d_fp, d_inv, st);
 }
 
 // token means of the sequences rows[0 .. *count) (or 0 .. n_max) of h, written to out[(dst[i] or i) * d ..] fp32

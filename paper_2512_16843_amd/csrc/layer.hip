@@ -427,6 +427,10 @@ llmc_status_t launch_linear(const void* A, int lda, const int32_t* a_rows, const
   return launch_gemm(a, dtype, st);
 }
 
+bool layer_pools_outputs(const llmc_layer_desc_t* L) {
+  return L->arch == 0 && (L->dtype == LLMC_F32 ? ln_pool_fits<float>(L->d) : ln_pool_fits<bf16_t>(L->d));
+}
+
 llmc_status_t launch_layer(const llmc_layer_desc_t* L, const void* d_h_in, void* d_h_out, int B, int S,
                            const int32_t* d_rows, const int32_t* d_count, void* ws, hipStream_t st,
                            float* pool_partial, uint8_t* pooled_flags) {

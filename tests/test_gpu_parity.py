@@ -1878,6 +1878,40 @@ def test_large_batch_equals_its_halves(L):
         st.close()
 
 
+@pytest.mark.parametrize("dtype,d,S,B,n_bank,policy", [
+    ("bf16", 128, 1, 5, 8, "lru"),          # one token: one chunk of one
+    ("bf16", 768, 64, 3, 16, "lru"),        # whole chunks
+    ("bf16", 1024, 130, 4, 6, "lru"),       # the widest row that is pooled on the way out; entries are evicted
+    ("bf16", 256, 577, 3, 4, "none"),       # ten chunks, the last of one token; the second batch is dropped
+    ("f32", 512, 65, 4, 8, "lru"),
+    ("f32", 768, 65, 4, 8, "lru"),          # too wide for it: the rows are pooled again
+])
+def test_means_and_next_keys_kept_at_insertion_are_those_of_the_stored_values(L, dtype, d, S, B, n_bank, policy):
+    """What a bank keeps beside the outputs that a call computes and stores (their token means and next-layer keys, formed
+    from the chunk sums of the block's last LayerNorm) has the bits that llmc_bank_pool_values forms from the values."""
+    from paper_2512_16843_amd.engine import GatedStack
+    say(f"kept means and next keys {dtype} d={d} S={S} B={B} bank {n_bank} {policy}")
+    cfg = W.scaled(small_cfg(0, dtype, d, d // 64, 2 * d, S, B), n_layers=2, n_bank=n_bank)
+    ws = W.make_layer_weights(cfg, seed=4)
+    Ps = W.make_projection(d, cfg.k, cfg.torch_dtype, seed=3, n_layers=2)
+    st = GatedStack(cfg, ws, Ps, keep_means=True, keep_next_keys=True, policy=L.EVICT_LRU if policy == "lru" else L.EVICT_NONE)
+    g = torch.Generator(device="cuda").manual_seed(S + d)
+    for tick in (1, 2):
+        h0 = torch.randn((B, S, d), generator=g, device="cuda").to(cfg.torch_dtype)
+        st.forward(h0, tau=2.0, flags=L.INSERT_ON_MISS, tick=tick)
+        torch.cuda.synchronize()
+        for l in range(2):
+            b = st.banks[l]
+            live = b.valid.bool()
+            kept = [b.act_pool[live].clone()] + ([b.next_fp[live].clone(), b.next_inv[live].clone()] if l == 0 else [])
+            L.llmc_bank_pool_values(b)
+            torch.cuda.synchronize()
+            again = [b.act_pool[live]] + ([b.next_fp[live], b.next_inv[live]] if l == 0 else [])
+            assert int(live.sum()) == min(n_bank, tick * B)
+            assert all(torch.equal(x, y) for x, y in zip(kept, again)), (tick, l)
+    st.close()
+
+
 @pytest.mark.parametrize("arch", [0, 1])
 def test_few_rows_and_many_rows_give_the_same_bits(L, arch):
     """A launch with few rows cuts the linear layers into smaller tiles with a deeper ring than a launch with many:

@@ -166,6 +166,20 @@ __device__ __forceinline__ double wave_sum(double v) {
   return butterfly_add<1>(v);
 }
 
+// Reads `bytes` (a multiple of 16) of `p` and drops them, so that a later reader finds them nearer: workgroup `i` of `n`, each
+// of `threads` threads, four vectors a thread and round.
+__device__ __forceinline__ void touch(const void* p, uint32_t bytes, int i, int n, int threads) {
+  const uint4* v = reinterpret_cast<const uint4*>(p);
+  const uint32_t count = bytes / 16, round = (uint32_t)threads * 4;
+  for (uint32_t at = i * round + threadIdx.x; at < count; at += n * round) {
+    uint4 x[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) x[u] = v[min(at + u * threads, count - 1)];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) asm volatile("" ::"v"(x[u].x), "v"(x[u].y), "v"(x[u].z), "v"(x[u].w));
+  }
+}
+
 // ---- host-side error plumbing ------------------------------------------------------
 llmc_status_t set_error(llmc_status_t st, const char* fmt, ...);
 llmc_status_t hip_error(hipError_t e, const char* what);

@@ -568,19 +568,6 @@ __device__ __forceinline__ int gemm_cost(int tiles, int nk, GemmCost c) {
 // small launch take.  Without the limit the 44 workgroups that 788 rows of a 768-wide block leave over read for 16 us beside
 // tiles of 8.
 constexpr uint32_t kGemmTouchBytes = 64 * 1024;
-// Read `bytes` of `p` and drop them: workgroup `i` of `n`, 16 KiB at a time.
-__device__ __forceinline__ void gemm_touch(const void* p, uint32_t bytes, int i, int n) {
-  const uint4* v = reinterpret_cast<const uint4*>(p);
-  const uint32_t count = bytes / 16;
-  for (uint32_t at = i * 1024 + threadIdx.x; at < count; at += n * 1024) {
-    uint4 x[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) x[u] = v[min(at + u * 256, count - 1)];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) asm volatile("" ::"v"(x[u].x), "v"(x[u].y), "v"(x[u].z), "v"(x[u].w));
-  }
-}
-
 template <int EPI>
 __global__ __launch_bounds__(256, 2) void gemm_bf16_dma_kernel(GemmArgs g) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds_dyn[];
@@ -610,7 +597,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_dma_kernel(GemmArgs g) {
       uint32_t left = (uint32_t)n * kGemmTouchBytes;
       for (int i = 0; i < 3; ++i) {
         const uint32_t bytes = min(g.ahead_bytes[i], left);
-        gemm_touch(g.ahead[i], bytes, blockIdx.x - busy, n);
+        touch(g.ahead[i], bytes, blockIdx.x - busy, n, 256);
         left -= bytes;
       }
       return;

@@ -1878,6 +1878,38 @@ def test_large_batch_equals_its_halves(L):
         st.close()
 
 
+@pytest.mark.parametrize("dtype,d,k,S,B", [
+    ("bf16", 768, 256, 65, 1027),      # two chunks, three rows in the last workgroup
+    ("bf16", 64, 64, 1, 1025),         # slices of four rows of the map, one token
+    ("f32", 192, 128, 130, 1024),      # the first batch that goes four rows to a workgroup, three chunks
+    ("bf16", 1088, 256, 2, 1026),      # slices of 68 rows: a remainder in every one
+])
+def test_keys_of_many_rows_are_those_of_a_few(L, dtype, d, k, S, B):
+    """Batches of 1024 rows and more are projected four rows to a workgroup: the same bits as in a small batch, for cosine
+    keys, their norms and sign-bit keys."""
+    say(f"keys of {B} rows {dtype} d={d} k={k} S={S}")
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(B)
+    h = torch.randn((B, S, d), generator=g, device="cuda").to(dt)
+    h[1] = 0                                                       # a zero key
+    P = (torch.randn((d, k), generator=g, device="cuda") * k ** -0.5).to(dt)
+    bias = torch.randn((k,), generator=g, device="cuda") * 0.1
+    def keys(x, c):
+        n = x.shape[0]
+        fp, inv = torch.empty((n, k), dtype=dt, device="cuda"), torch.empty((n,), device="cuda")
+        bits = torch.empty((n, k // 32), dtype=torch.int32, device="cuda")
+        ws = torch.empty((L.llmc_fingerprint_workspace_bytes(n, S, d),), dtype=torch.uint8, device="cuda")
+        L.llmc_fingerprint(x, P, c, fp, inv, ws)
+        L.llmc_fingerprint_bits(x, P, c, bits, ws)
+        torch.cuda.synchronize()
+        return fp, inv, bits
+    for c in (None, bias):
+        many = keys(h, c)
+        for rows in (slice(0, 9), slice(510, 515), slice(B - 6, B)):
+            few = keys(h[rows].contiguous(), c)
+            assert all(torch.equal(m[rows], f) for m, f in zip(many, few)), (rows, c is None)
+
+
 @pytest.mark.parametrize("dtype,d,S,B,n_bank,policy", [
     ("bf16", 128, 1, 5, 8, "lru"),          # one token: one chunk of one
     ("bf16", 768, 64, 3, 16, "lru"),        # whole chunks

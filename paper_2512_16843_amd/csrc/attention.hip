@@ -143,6 +143,10 @@ __global__ __launch_bounds__(AttnCfg::THREADS) void attention_mfma_kernel(const 
     LLMC_ATTN_LOAD(0)
     LLMC_ATTN_STORE(0)
     __syncthreads();
+    // The queries are waited for HERE: left to the first product, that wait counts outstanding loads inside the loop, where
+    // the next tile's loads have just been issued, and every tile waits for them.
+#pragma unroll
+    for (int ks = 0; ks < 4; ++ks) asm volatile("" : "+v"(fq[ks]));
 
     for (int t = 0; t < n_tiles; ++t) {
       const int buf = t & 1;

@@ -63,6 +63,21 @@ struct GemmArgs {
   int act;                         // 0 none, 1 GELU erf, 2 GELU tanh
 };
 
+// What a workgroup without a tile reads of the weights that follow: four rounds of 16 KiB, about as long as the tiles of a
+// small launch take.  Without the limit the 44 workgroups that 788 rows of a 768-wide block leave over read for 16 us beside
+// tiles of 8.
+constexpr uint32_t kGemmTouchBytes = 64 * 1024;
+// by the workgroups (of 256 threads) from number `busy` on
+__device__ __forceinline__ void gemm_read_ahead(const GemmArgs& g, int busy) {
+  const int n = gridDim.x - busy;
+  uint32_t left = (uint32_t)n * kGemmTouchBytes;
+  for (int i = 0; i < 3; ++i) {
+    const uint32_t bytes = min(g.ahead_bytes[i], left);
+    touch(g.ahead[i], bytes, blockIdx.x - busy, n, 256);
+    left -= bytes;
+  }
+}
+
 // the fp32 form (dense_f32.hip)
 llmc_status_t launch_gemm_f32(const GemmArgs& g, hipStream_t st);
 
@@ -564,10 +579,6 @@ __device__ __forceinline__ int gemm_cost(int tiles, int nk, GemmCost c) {
          (rest == 0 ? 0 : rest <= kGemmGrid / 2 ? c.alone_fixed + nk * c.alone_step : c.both_fixed + nk * c.both_step);
 }
 
-// What a workgroup without a tile reads of the weights that follow: four rounds of 16 KiB, about as long as the tiles of a
-// small launch take.  Without the limit the 44 workgroups that 788 rows of a 768-wide block leave over read for 16 us beside
-// tiles of 8.
-constexpr uint32_t kGemmTouchBytes = 64 * 1024;
 template <int EPI>
 __global__ __launch_bounds__(256, 2) void gemm_bf16_dma_kernel(GemmArgs g) {
   extern __shared__ __attribute__((aligned(16))) uint16_t lds_dyn[];
@@ -593,13 +604,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_dma_kernel(GemmArgs g) {
     offer(4, m32 * n64, few);
     const int busy = (tiles + 7) & ~7;                   // workgroups beyond have no tile, in any order of the tiles
     if ((int)blockIdx.x >= busy) {
-      const int n = gridDim.x - busy;
-      uint32_t left = (uint32_t)n * kGemmTouchBytes;
-      for (int i = 0; i < 3; ++i) {
-        const uint32_t bytes = min(g.ahead_bytes[i], left);
-        touch(g.ahead[i], bytes, blockIdx.x - busy, n, 256);
-        left -= bytes;
-      }
+      gemm_read_ahead(g, busy);
       return;
     }
   } else {

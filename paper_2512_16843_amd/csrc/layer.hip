@@ -13,6 +13,8 @@
 // fp32 runs are translation units of their own.
 #include "common.h"
 #include <algorithm>
+#include <initializer_list>
+#include <utility>
 #include "gemm.h"
 
 namespace llmc {
@@ -320,26 +322,26 @@ static llmc_status_t layer_t(const llmc_layer_desc_t* L, const void* h_in, void*
     a.resid = resid; a.ldr = N; a.r_rows = r_rows; a.out = out; a.ldo = N; a.o_rows = o_rows;
     return launch_gemm(a, L->dtype, st);
   };
-  // The first product's workgroups that find no tile read the weights of the other three: with few rows those layers are
-  // bound by the latency of their weights, which is that of the memory-side cache then and not that of HBM.  (Stacks of 12
-  // 768-wide layers whose weights come from HBM, microseconds: one sequence of 128 tokens 1059 -> 1015, prefix keys with 2
-  // of 16 sequences computed 2930 -> 2842.)  Nothing is read where no row is computed, or every workgroup has a tile.
-  GemmArgs with_ahead = g;
-  const void* const rest[3] = {L->d_wo, L->d_w1, L->d_w2};
-  const size_t rest_bytes[3] = {(size_t)d * d * e, (size_t)d * dff * e, (size_t)d * dff * e};
-  for (int i = 0; i < 3; ++i)
-    if (rest_bytes[i] < (1ull << 28)) { with_ahead.ahead[i] = rest[i]; with_ahead.ahead_bytes[i] = (uint32_t)rest_bytes[i]; }
-  auto gemm_qkv = [&](const void* A, const int32_t* a_rows) {
-    const GemmArgs plain = g;
-    g = with_ahead;
-    const llmc_status_t s = gemm(A, d, a_rows, L->d_wqkv, L->d_bqkv, 3 * d, d, 0, nullptr, nullptr, qkv, nullptr);
-    g = plain;
-    return s;
+  // Workgroups of the first two products that find no tile read the weights of those that follow: with few rows these are
+  // bound by the latency of their weights, which is that of the memory-side cache then and not that of HBM.  Nothing is
+  // read where no row is computed, or every workgroup has a tile.  (Stacks of 12 768-wide layers whose weights come from
+  // HBM, microseconds: one sequence of 128 tokens 1059 -> 1015, prefix keys with 2 of 16 sequences computed 2930 -> 2842;
+  // with the second product too, 4 of 37 sequences of 197 tokens 1168 -> 1131, 24 1024-wide layers with 32 of 256 sequences
+  // 6370 -> 6251.)  The fp32 products keep their loads in flight long enough: with it 8 x 128 tokens took 1924 for 1897.
+  auto read_ahead = [&](std::initializer_list<std::pair<const void*, size_t>> weights) {
+    int i = 0;
+    for (const auto& w : weights)
+      if (e == 2 && w.second * e < (1ull << 28)) { g.ahead[i] = w.first; g.ahead_bytes[i++] = (uint32_t)(w.second * e); }
+    for (; i < 3; ++i) { g.ahead[i] = nullptr; g.ahead_bytes[i] = 0; }
   };
+  const std::pair<const void*, size_t> wo = {L->d_wo, (size_t)d * d}, w1 = {L->d_w1, (size_t)d * dff}, w2 = {L->d_w2, (size_t)d * dff};
   if (L->arch == 0) {
-    LLMC_TRY(gemm_qkv(h_in, rows));
+    read_ahead({wo, w1, w2});
+    LLMC_TRY(gemm(h_in, d, rows, L->d_wqkv, L->d_bqkv, 3 * d, d, 0, nullptr, nullptr, qkv, nullptr));
     LLMC_TRY(launch_attention<T>(qkv, ctx, S, d, L->n_heads, false, count, B, st));
+    read_ahead({w1, w2});
     LLMC_TRY(gemm(ctx, d, nullptr, L->d_wo, L->d_bo, d, d, 0, h_in, rows, t0, nullptr));
+    read_ahead({});
     LLMC_TRY(launch_ln<T>(t0, nullptr, t1, nullptr, L->d_ln1_g, L->d_ln1_b, L->ln_eps, d, S, count, B, st));
     LLMC_TRY(gemm(t1, d, nullptr, L->d_w1, L->d_b1, dff, d, act, nullptr, nullptr, ff, nullptr));
     LLMC_TRY(gemm(ff, dff, nullptr, L->d_w2, L->d_b2, d, dff, 0, t1, nullptr, t0, nullptr));
@@ -350,9 +352,12 @@ static llmc_status_t layer_t(const llmc_layer_desc_t* L, const void* h_in, void*
       LLMC_TRY(launch_ln<T>(t0, nullptr, h_out, rows, L->d_ln2_g, L->d_ln2_b, L->ln_eps, d, S, count, B, st));
   } else {
     LLMC_TRY(launch_ln<T>(h_in, rows, t1, nullptr, L->d_ln1_g, L->d_ln1_b, L->ln_eps, d, S, count, B, st));
-    LLMC_TRY(gemm_qkv(t1, nullptr));
+    read_ahead({wo, w1, w2});
+    LLMC_TRY(gemm(t1, d, nullptr, L->d_wqkv, L->d_bqkv, 3 * d, d, 0, nullptr, nullptr, qkv, nullptr));
     LLMC_TRY(launch_attention<T>(qkv, ctx, S, d, L->n_heads, true, count, B, st));
+    read_ahead({w1, w2});
     LLMC_TRY(gemm(ctx, d, nullptr, L->d_wo, L->d_bo, d, d, 0, h_in, rows, t0, nullptr));
+    read_ahead({});
     LLMC_TRY(launch_ln<T>(t0, nullptr, t1, nullptr, L->d_ln2_g, L->d_ln2_b, L->ln_eps, d, S, count, B, st));
     LLMC_TRY(gemm(t1, d, nullptr, L->d_w1, L->d_b1, dff, d, act, nullptr, nullptr, ff, nullptr));
     LLMC_TRY(gemm(ff, dff, nullptr, L->d_w2, L->d_b2, d, dff, 0, t0, nullptr, h_out, rows));

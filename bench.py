@@ -49,11 +49,11 @@ CSRC = os.path.join(ROOT, "paper_2512_16843_amd", "csrc")
 MEASURED_TRAFFIC = {
     # profiles/kernel_bench_dense_block_trace_and_counters.txt: one block over 28 sequences (the headline's mean miss
     # count is 27.7), average over the block's launches of the kernel
-    "gemm_bf16_kernel": (144384056, ['gemm.h', 'mma.h', 'layer.hip'], "e294b08f5f05dcd6"),
-    "attention_kernel": (132225077, ['attention.hip', 'mma.h'], "1a70b3143e344e57"),
+    "gemm_bf16_kernel": (137658876, ['gemm.h', 'mma.h', 'layer.hip'], "56c36e91b970a475"),
+    "attention_kernel": (66169024, ['attention.hip', 'mma.h'], "ce70fb0098635d08"),
     # profiles/kernel_bench_bert_base_shape_trace_and_hbm_counters.txt: 64 sequences, bank of 16384 keys
-    "pool_kernel": (39023274, ['fingerprint.hip'], "43d5991dbbd64f38"),
-    "match_stream_kernel": (9133056, ['match.hip', 'mma.h'], "93b4d35349c0c7b5"),
+    "pool_kernel": (39007189, ['fingerprint.hip'], "f7b9d58d5c5b3af0"),
+    "match_stream_kernel": (9133056, ['match.hip', 'mma.h'], "887dfa90c0a52454"),
 }
 
 

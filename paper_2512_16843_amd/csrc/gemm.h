@@ -93,15 +93,16 @@ __device__ __forceinline__ float apply_act(float v, int act) {
 // `out` and the epilogue needs no LDS.  Every tiling accumulates an output element over k in ascending order with the
 // same instruction, so the bits of a row do not depend on how many rows are computed with it.
 //
-// What bounds it: power first (a loop of nothing but these matrix instructions on such values runs at 1650 TFLOP/s and a
-// clock of 1.7 GHz; with the fragment reads from LDS it reaches 1400, with the loads as well 950 to 1100), so bytes per flop
-// count on every level even where their latency is hidden: a wavefront owns 64 x 96 outputs (64 x 32 before: half the bytes
-// read from LDS), a compute unit two tiles of 128 x 192.  Then the epilogue, which only the other workgroup's main loop
+// What bounds it: partly power, inferred from the clock (a loop of nothing but these matrix instructions on such values runs
+// at 1650 TFLOP/s and 1.7 GHz; with the fragment reads from LDS it reaches 1400, with the loads as well 950 to 1100).  Not it alone: counters at 24,576
+// rows show the matrix pipe 35 to 37 % busy at 2.1 to 2.3 GHz and wavefronts waiting 40 to 49 % of their cycles.  So bytes per flop
+// count on every level even where their latency is hidden: a wavefront owns 64 x 96 outputs (64 x 32 before: 1.8 times the
+// bytes read from LDS), a compute unit two tiles of 128 x 192.  Then the epilogue, which only the other workgroup's main loop
 // covers: an activation chosen at compile time (GELU over 24,576 x 3072 outputs: 186 -> 145 us for the layer).
 // The four layers of a 768-wide block (microseconds, before / now): 24,576 rows 450 / 396, 9984 rows 199 / 178, 8192 rows
 // 171 / 157, 4096 rows 106 / 105, 788 rows 46 / 39, 128 rows 31 / 30; 4096 rows of 1024: 149 / 142.
 // Timed and not taken at 24,576 and 32,768 rows: 256 x 256 tiles with eight wavefronts of 128 x 64 and one workgroup to a
-// compute unit (3 % less at 1024 wide, where the tile count divides by 256, 20 to 60 % more elsewhere); steps of 32 columns
+// compute unit (within 2 % over 32,768 rows of 1024, where the tile count divides by 256, 20 to 60 % more elsewhere); steps of 32 columns
 // with three to five stages (64-byte rows of a panel: 7 to 20 % more); a third stage for A (4 % more).
 
 // what follows the product: 0 nothing, 1 GELU (erf), 2 GELU (tanh), 3 the residual is added

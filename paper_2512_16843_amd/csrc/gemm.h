@@ -3,6 +3,7 @@
 #pragma once
 #include <type_traits>
 #include "common.h"
+#include "gemm_rule.h"
 #include "mma.h"
 
 namespace llmc {
@@ -94,16 +95,20 @@ __device__ __forceinline__ float apply_act(float v, int act) {
 // same instruction, so the bits of a row do not depend on how many rows are computed with it.
 //
 // What bounds it: partly power, inferred from the clock (a loop of nothing but these matrix instructions on such values runs
-// at 1650 TFLOP/s and 1.7 GHz; with the fragment reads from LDS it reaches 1400, with the loads as well 950 to 1100).  Not it alone: counters at 24,576
-// rows show the matrix pipe 35 to 37 % busy at 2.1 to 2.3 GHz and wavefronts waiting 40 to 49 % of their cycles.  So bytes per flop
-// count on every level even where their latency is hidden: a wavefront owns 64 x 96 outputs (64 x 32 before: 1.8 times the
-// bytes read from LDS), a compute unit two tiles of 128 x 192.  Then the epilogue, which only the other workgroup's main loop
-// covers: an activation chosen at compile time (GELU over 24,576 x 3072 outputs: 186 -> 145 us for the layer).
-// The four layers of a 768-wide block (microseconds, before / now): 24,576 rows 450 / 396, 9984 rows 199 / 178, 8192 rows
-// 171 / 157, 4096 rows 106 / 105, 788 rows 46 / 39, 128 rows 31 / 30; 4096 rows of 1024: 149 / 142.
+// at 1650 TFLOP/s and 1.7 GHz; with the fragment reads from LDS it reaches 1400, with the loads as well 950 to 1100).  Not it
+// alone: counters at 24,576 rows show the matrix pipe 35 to 37 % busy at 2.1 to 2.3 GHz and wavefronts waiting 40 to 49 % of
+// their cycles.  So bytes per flop count on every level even where their latency is hidden: a wavefront owns 64 x 96 outputs
+// (64 x 32 before: 1.8 times the bytes read from LDS), a compute unit two tiles of 128 x 192.  Then the epilogue, which only
+// the other workgroup's main loop covers: an activation chosen at compile time (GELU over 24,576 x 3072 outputs: 186 -> 145 us
+// for the layer).
+// The four layers of a 768-wide block (microseconds, one run): eight wavefronts of 64 x 32 on 128 x 128 tiles / now: 32,768
+// rows 663 / 564, 24,576 rows 491 / 426, 10,240 rows 204 / 186, 8192 rows 180 / 168, 4096 rows 108 / 107, 2048 rows 73 / 66,
+// 788 rows 48 / 41, 128 rows 30 / 29; 4096 rows of 1024: 156 / 150.  Slower than those eight wavefronts: shallow products of
+// many rows, where the epilogue of four wavefronts has less behind it to hide (128 wide: 24,576 rows 45 / 48, 32,768 rows
+// 51 / 54; 64 wide, 6144 rows and more: 2 to 3 %).
 // Timed and not taken at 24,576 and 32,768 rows: 256 x 256 tiles with eight wavefronts of 128 x 64 and one workgroup to a
-// compute unit (within 2 % over 32,768 rows of 1024, where the tile count divides by 256, 20 to 60 % more elsewhere); steps of 32 columns
-// with three to five stages (64-byte rows of a panel: 7 to 20 % more); a third stage for A (4 % more).
+// compute unit (within 2 % over 32,768 rows of 1024, where the tile count divides by 256, 20 to 60 % more elsewhere); steps of
+// 32 columns with three to five stages (64-byte rows of a panel: 7 to 20 % more); a third stage for A (4 % more).
 
 // what follows the product: 0 nothing, 1 GELU (erf), 2 GELU (tanh), 3 the residual is added
 constexpr int kEpiPlain = 0, kEpiGeluErf = 1, kEpiGeluTanh = 2, kEpiResidual = 3;
@@ -384,8 +389,9 @@ __device__ __forceinline__ void gemm_ring_tiles(const GemmArgs& g, int M, uint16
 
 // ---- fewer rows: a ring of its own per tile ----------------------------------------------------------------
 // A launch with few tiles lasts as long as the latency of its loads times the steps over the steps in flight, and a
-// step as long as its own fragments take to arrive from LDS.  (788 rows of a 768-wide block: 17.7 -> 12.8 us for K = 3072.)  So: smaller tiles, more stages, and a whole step's
-// fragments held in registers: those of step kt are read from LDS behind the multiplies of step kt - 1 that free theirs.
+// step as long as its own fragments take to arrive from LDS.  (788 rows of a 768-wide block: 17.7 -> 12.8 us for K = 3072.)
+// So: smaller tiles, more stages, and a whole step's fragments held in registers: those of step kt are read from LDS behind
+// the multiplies of step kt - 1 that free theirs.
 // WM x WN wavefronts multiply (they fetch PC blocks of eight rows a stage), the others only load (PL blocks).
 template <int BM_, int BN_, int WM_, int WN_, int STAGES_, int PC_, int PL_>
 struct GemmStep {
@@ -563,22 +569,12 @@ typedef GemmStep<64, 128, 2, 2, 3, 6, 6> GemmLow;      // 72 KiB
 typedef GemmStep<64, 64, 2, 2, 4, 4, 4> GemmTiny;      // 64 KiB
 typedef GemmStep<32, 64, 1, 2, 6, 2, 4> GemmFew;       // 72 KiB
 constexpr size_t kGemmLdsBytes = GemmBig::LDS_BYTES;
-constexpr int kGemmGrid = 512;                         // two workgroups on each of 256 compute units
 static_assert(GemmMid::LDS_BYTES <= kGemmLdsBytes && GemmLow::LDS_BYTES <= kGemmLdsBytes &&
               GemmTiny::LDS_BYTES <= kGemmLdsBytes && GemmFew::LDS_BYTES <= kGemmLdsBytes, "one launch serves all tilings");
-
-// Time of `tiles` tiles of nk steps (units of 10 ns): whole rounds of 512 tiles, two to a compute unit, and what is left over,
-// one to a compute unit if that many are enough.  A round is a tile's fixed part and its steps; both are fits to the
-// layers of 256-, 768- and 1024-wide blocks at 64 to 32,768 rows, each tiling forced in turn, weights from HBM.  The rule
-// takes the fastest tiling or one within 5 % of it at these sizes: at 768 columns and K = 3072, 128 x 192 / 128 x 128 / 64 x
-// 128 / 64 x 64 / 32 x 64 tiles take 116 / 135 / 166 / 208 / - us for 24,576 rows, 65 / 52 / 72 / 87 / - for 9984, 45 / 39 /
-// 36 / 37 / 47 for 4096, 43 / 37 / 20 / 24 / 25 for 2048, 43 / 37 / 19 / 13 / 17 for 788, 35 / 27 / 17 / 11 / 10 for 256.
-struct GemmCost { int both_fixed, both_step, alone_fixed, alone_step; };
-__device__ __forceinline__ int gemm_cost(int tiles, int nk, GemmCost c) {
-  const int rest = tiles % kGemmGrid;
-  return (tiles / kGemmGrid) * (c.both_fixed + nk * c.both_step) +
-         (rest == 0 ? 0 : rest <= kGemmGrid / 2 ? c.alone_fixed + nk * c.alone_step : c.both_fixed + nk * c.both_step);
-}
+template <class C, int PATH>
+constexpr bool gemm_same_tile = C::BM == kGemmTileRows[PATH] && C::BN == kGemmTileCols[PATH];
+static_assert(gemm_same_tile<GemmBig, kGemmBig> && gemm_same_tile<GemmMid, kGemmMid> && gemm_same_tile<GemmLow, kGemmLow> &&
+              gemm_same_tile<GemmTiny, kGemmTiny> && gemm_same_tile<GemmFew, kGemmFew>, "the rule counts these tiles");
 
 template <int EPI>
 __global__ __launch_bounds__(256, 2) void gemm_bf16_dma_kernel(GemmArgs g) {
@@ -586,35 +582,16 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_dma_kernel(GemmArgs g) {
   const int n_seq = g.count ? min(*g.count, g.max_seqs) : g.max_seqs;
   const int M = n_seq * g.S;
   if (M <= 0) return;
-  const int nk = g.K / 64;
-  const int n64 = (g.N + 63) / 64, n128 = (n64 + 1) / 2, n192 = (n64 + 2) / 3;
-  const int m128 = (M + 127) / 128, m64 = (M + 63) / 64, m32 = (M + 31) / 32;
-  constexpr int act = EPI == kEpiGeluErf || EPI == kEpiGeluTanh ? 200 : 0;    // alone, nothing covers a large tile's epilogue
-  constexpr GemmCost big = {860, 117, 600 + act, 82}, mid = {600, 89, 150 + act, 75}, low = {350, 66, 260, 39},
-                     tiny = {100, 44, 150, 23}, few = {100, 30, 130, 19};
-  int path = 0, tiles = m128 * n192;
-  if (nk < 2 || tiles <= 4 * kGemmGrid) {
-    int best = nk < 2 ? 0x7FFFFFFF : gemm_cost(tiles, nk, big);            // the ring starts with two steps
-    auto offer = [&](int p, int t, GemmCost c) {
-      const int cost = gemm_cost(t, nk, c);
-      if (cost < best) { best = cost; path = p; tiles = t; }
-    };
-    if (nk >= 2) offer(1, m128 * n128, mid);
-    offer(2, m64 * n128, low);
-    offer(3, m64 * n64, tiny);
-    offer(4, m32 * n64, few);
-    const int busy = (tiles + 7) & ~7;                   // workgroups beyond have no tile, in any order of the tiles
-    if ((int)blockIdx.x >= busy) {
-      gemm_read_ahead(g, busy);
-      return;
-    }
-  } else {
-    path = n192 * (big.both_fixed + nk * big.both_step) > n128 * (mid.both_fixed + nk * mid.both_step) ? 1 : 0;
+  const GemmPick pick = gemm_pick(M, g.N, g.K / 64, EPI == kEpiGeluErf || EPI == kEpiGeluTanh);
+  const int busy = (pick.tiles + 7) & ~7;                // workgroups beyond have no tile, in any order of the tiles
+  if ((int)blockIdx.x >= busy) {
+    gemm_read_ahead(g, busy);
+    return;
   }
-  if (path == 0) gemm_ring_tiles<GemmBig, EPI>(g, M, lds_dyn);
-  else if (path == 1) gemm_ring_tiles<GemmMid, EPI>(g, M, lds_dyn);
-  else if (path == 2) gemm_step_tiles<GemmLow, EPI>(g, M, lds_dyn);
-  else if (path == 3) gemm_step_tiles<GemmTiny, EPI>(g, M, lds_dyn);
+  if (pick.path == kGemmBig) gemm_ring_tiles<GemmBig, EPI>(g, M, lds_dyn);
+  else if (pick.path == kGemmMid) gemm_ring_tiles<GemmMid, EPI>(g, M, lds_dyn);
+  else if (pick.path == kGemmLow) gemm_step_tiles<GemmLow, EPI>(g, M, lds_dyn);
+  else if (pick.path == kGemmTiny) gemm_step_tiles<GemmTiny, EPI>(g, M, lds_dyn);
   else gemm_step_tiles<GemmFew, EPI>(g, M, lds_dyn);
 }
 

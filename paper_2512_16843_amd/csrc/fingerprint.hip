@@ -135,18 +135,21 @@ __device__ __forceinline__ void pool_sequence(const T* __restrict__ seq, int S, 
 // whole wavefronts, so that the butterflies of the norm read live lanes only (at most 1024 since k and cgs * parts are)
 static inline int project_threads(int cgs, int parts, int k) { return (std::max(cgs * parts, k) + 63) & ~63; }
 
-// A workgroup reads the whole map by itself, and a single compute unit takes long to fetch so much from memory.  With few rows
-// (at most kProjectFewRows, so that most compute units are idle) kProjectHelpers more workgroups on each of the eight XCDs
-// that workgroups are dealt to in turn read a slice of the map each, into the L2 that the projecting ones read from; they
-// leave at once where no row of their XCD is projected.  Maps of 768 x 256 from HBM: one bf16 row 14.3 -> 10.9 us, 64
-// rows 12.9 -> 11.4, eight fp32 rows 23.0 -> 16.2; every key copied: 4.5 -> 4.1 (no change).
-constexpr int kProjectHelpers = 16, kProjectFewRows = 256;
-static inline int project_grid(int rows) {
-  return rows <= kProjectFewRows ? ((rows + 7) & ~7) + 8 * kProjectHelpers : rows;
+// A workgroup reads the whole map by itself, and a single compute unit takes long to fetch so much from memory.  With few rows,
+// so that compute units are idle, kProjectHelpers more workgroups on each of the eight XCDs that workgroups are dealt to in
+// turn read a slice of the map each, into the L2 that the projecting ones read from; they leave at once where no row of their
+// XCD is projected.  Maps of 768 x 256 from HBM: one bf16 row 14.3 -> 10.9 us, 64 rows 12.9 -> 11.4, eight fp32 rows 23.0 ->
+// 16.2; every key copied: 4.5 -> 4.1 (no change).  Up to 256 rows, or 224 where every row is projected
+// (`every`) and a workgroup of 1024 threads fills a compute unit, so that the helpers wait for places: time without / with them
+// (768 x 256) 224 rows 1.01 bf16 and 1.05 fp32, 232 to 256 rows 0.95 to 0.96; (768 x 128) 256 rows 0.99 and 1.09; but 256 rows
+// of 1024 x 256 of which 224 arrive with their keys: a stack of 24 layers 6297 us without, 6259 with them.
+constexpr int kProjectHelpers = 16;
+static inline int project_grid(int rows, int threads, bool every) {
+  return rows <= (every && threads == 1024 ? 224 : 256) ? ((rows + 7) & ~7) + 8 * kProjectHelpers : rows;
 }
 
-// grid project_grid(B); block CG * PARTS threads (rounded up to wavefronts): thread (cg, part) owns the four output columns 4*cg .. 4*cg+3
-// over the part-th slice of d; slices are then added in ascending order.
+// grid project_grid(B); block CG * PARTS threads (rounded up to wavefronts): thread (cg, part) owns the four output columns
+// 4*cg .. 4*cg+3 over the part-th slice of d; slices are then added in ascending order.
 template <typename T>
 __global__ __launch_bounds__(1024) void project_kernel(const float* __restrict__ partial, int n_chunks, int S, int d,
                                                        const T* __restrict__ P, const float* __restrict__ bias, int k,
@@ -535,11 +538,12 @@ static llmc_status_t fingerprint_t(const T* h, int B, int S, int d, const T* P, 
                        n_chunks, pooled_valid, (const int32_t*)nullptr, (const int32_t*)nullptr, key_index); }
     LLMC_LAUNCH_CHECK("pool_kernel");
   }
-  if (!inline_pool && !pooled_in && !pooled_valid && !key_in && !key_index && project_many(B, d, k))
+  const bool every = !pooled_in && !pooled_valid && !key_in && !key_index;          // no row arrives with its mean or key
+  if (!inline_pool && every && project_many(B, d, k))
     return launch_project_many<T>(partial, n_chunks, S, d, P, bias, k, fp, inv, bits, nullptr, B, st);
   {
     ProfScope ps_("project_kernel", st);
-    LLMC_KERNEL_GGL(project_kernel<T>, dim3(project_grid(B)), dim3(threads),
+    LLMC_KERNEL_GGL(project_kernel<T>, dim3(project_grid(B, threads, every)), dim3(threads),
                        (size_t)(d + parts * k + (inline_pool ? R * d : 0)) * sizeof(float), st, partial, n_chunks, S, d, P,
                        bias, k, parts, fp, inv, bits, pooled_in, pooled_valid, key_in, key_inv_in, (const int32_t*)nullptr,
                        (const int32_t*)nullptr, inline_pool ? h : (const T*)nullptr, G, R, key_index,
@@ -621,9 +625,9 @@ static llmc_status_t project_rows_t(const float* means, int n_max, int d, const 
   if (!rows && !count && project_many(n_max, d, k))
     return launch_project_many<T>(nullptr, 0, 1, d, P, bias, k, fp, inv, nullptr, means, n_max, st);
   const int cgs = k / 4;
-  const int parts = std::max(1, std::min(1024 / cgs, 16));
+  const int parts = std::max(1, std::min(1024 / cgs, 16)), threads = project_threads(cgs, parts, k);
   ProfScope ps_("project_kernel", st);
-  LLMC_KERNEL_GGL(project_kernel<T>, dim3(project_grid(n_max)), dim3(project_threads(cgs, parts, k)),
+  LLMC_KERNEL_GGL(project_kernel<T>, dim3(project_grid(n_max, threads, !rows && !count)), dim3(threads),
                      (size_t)(d + parts * k) * sizeof(float), st, (const float*)nullptr, 0, 1, d, P, bias, k, parts, fp, inv,
                      (uint32_t*)nullptr, means, (const uint8_t*)nullptr, (const T*)nullptr, (const float*)nullptr, rows,
                      count, (const T*)nullptr, 0, 0, (const int32_t*)nullptr, (const int32_t*)nullptr, (float*)nullptr,
@@ -659,11 +663,11 @@ static llmc_status_t keep_stored_t(const float* partial, int n_max, int S, int d
     return LLMC_OK;
   }
   const int cgs = k / 4;
-  const int parts = std::max(1, std::min(1024 / cgs, 16));
+  const int parts = std::max(1, std::min(1024 / cgs, 16)), threads = project_threads(cgs, parts, k);
   ProfScope ps_("project_kernel", st);
-  LLMC_KERNEL_GGL(project_kernel<T>, dim3(project_grid(n_max)), dim3(project_threads(cgs, parts, k)), (size_t)(d + parts * k) * sizeof(float),
-                  st, partial, n_chunks, S, d, P, bias, k, parts, fp, inv, (uint32_t*)nullptr, (const float*)nullptr,
-                  (const uint8_t*)nullptr, (const T*)nullptr, (const float*)nullptr, dst, count, (const T*)nullptr, 0, 0,
+  LLMC_KERNEL_GGL(project_kernel<T>, dim3(project_grid(n_max, threads, false)), dim3(threads),
+                  (size_t)(d + parts * k) * sizeof(float), st, partial, n_chunks, S, d, P, bias, k, parts, fp, inv,
+                  (uint32_t*)nullptr, (const float*)nullptr, (const uint8_t*)nullptr, (const T*)nullptr, (const float*)nullptr, dst, count, (const T*)nullptr, 0, 0,
                   (const int32_t*)nullptr, rows, means, n_max);
   LLMC_LAUNCH_CHECK("project_kernel");
   return LLMC_OK;

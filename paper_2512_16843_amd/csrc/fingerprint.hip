@@ -338,11 +338,17 @@ __global__ __launch_bounds__(1024) void project_kernel(const float* __restrict__
 // is fetched and unpacked once for all of them.  Rows come from the chunk sums, or from `means` if given; k = 64, 128 or 256,
 // so that the threads that add the slices are whole wavefronts of one row: thread (row, column) = (tid / k, tid % k).
 // Bound: vector FMAs and the map's way out of L2; 4096 rows through 768 x 256 bf16, six chunks each: 158 -> 50 us.
-constexpr int kProjectRows = 4, kProjectManyRows = 1024;
-constexpr size_t kProjectManyLds = 79 * 1024;     // with the statics: two workgroups to a compute unit
+// Taken where the workgroups of one row each no longer fit the chip at once (4 k threads: 256 of k = 256, 512 of k = 128), time
+// of one row / four rows a workgroup, bf16, 768 wide: k = 256 256 rows 0.81, 257 1.40, 1024 2.6; k = 128 512 rows 0.81, 640
+// 1.12, 1024 1.38; k = 64 1024 rows 0.85, 1536 1.01, 2048 1.15 (128 wide 0.99, 1.40, 1.47).  Its LDS lets one workgroup to a
+// compute unit do for k = 256 and 128 (4096 x 256: 257 rows 1.44, 4096 rows 2.8; 4096 x 128: 513 rows 1.11, 4096 rows 1.36),
+// not for k = 64 (4096 x 64: 0.6 at 4096 rows).
+constexpr int kProjectRows = 4;
+constexpr size_t kProjectManyLds = 158 * 1024, kProjectManyLdsTwo = 79 * 1024;     // with the statics: one, two to a compute unit
 static inline bool project_many(int rows, int d, int k) {
-  return rows >= kProjectManyRows && (k == 64 || k == 128 || k == 256) &&
-         (size_t)(d + 16 * k) * kProjectRows * sizeof(float) <= kProjectManyLds;
+  const size_t lds = (size_t)(d + 16 * k) * kProjectRows * sizeof(float);
+  return k == 256 ? rows > 256 && lds <= kProjectManyLds
+                  : k == 128 ? rows > 512 && lds <= kProjectManyLds : k == 64 && rows >= 1536 && lds <= kProjectManyLdsTwo;
 }
 
 // grid (ceil(n / kProjectRows)); block 4 k = k / 4 column groups x 16 slices of d; LDS (d + 16 k) * kProjectRows floats
@@ -410,18 +416,12 @@ __global__ __launch_bounds__(1024) void project_many_kernel(const float* __restr
         for (int e = 0; e < 4; ++e) v[r][e] = fmaf(pi[r], w[e], v[r][e]);
     };
     constexpr int U = 4;
-    int i = i0;
-    for (; i + U <= i1; i += U) {
+    for (int i = i0; i < i1; i += U) {                         // d is a multiple of 64: slices are multiples of four rows
       float w[U][4];
 #pragma unroll
       for (int u = 0; u < U; ++u) unpack(col + (size_t)(i + u) * k, w[u]);
 #pragma unroll
       for (int u = 0; u < U; ++u) add(i + u, w[u]);
-    }
-    for (; i < i1; ++i) {
-      float w[4];
-      unpack(col + (size_t)i * k, w);
-      add(i, w);
     }
 #pragma unroll
     for (int r = 0; r < R; ++r)

@@ -1880,13 +1880,18 @@ def test_large_batch_equals_its_halves(L):
 
 @pytest.mark.parametrize("dtype,d,k,S,B", [
     ("bf16", 768, 256, 65, 1027),      # two chunks, three rows in the last workgroup
-    ("bf16", 64, 64, 1, 1025),         # slices of four rows of the map, one token
-    ("f32", 192, 128, 130, 1024),      # the first batch that goes four rows to a workgroup, three chunks
-    ("bf16", 1088, 256, 2, 1026),      # slices of 68 rows: a remainder in every one
+    ("bf16", 64, 64, 1, 1537),         # slices of four rows of the map, one token, one row in the last workgroup
+    ("f32", 192, 128, 130, 514),       # two rows in the last workgroup, three chunks
+    ("bf16", 1088, 256, 2, 1026),      # slices of 68 rows
+    ("bf16", 128, 256, 577, 257),      # the first batch of 256-value keys that goes four rows to a workgroup, ten chunks
+    ("f32", 64, 128, 3, 513),          # ... of 128 values
+    ("bf16", 4032, 64, 1, 1536),       # ... of 64 values, at the widest rows for them
+    ("bf16", 6016, 256, 1, 259),       # the widest rows whose sums fit the LDS
+    ("f32", 4096, 256, 1, 258),        # the widest rows of fp32
 ])
 def test_keys_of_many_rows_are_those_of_a_few(L, dtype, d, k, S, B):
-    """Batches of 1024 rows and more are projected four rows to a workgroup: the same bits as in a small batch, for cosine
-    keys, their norms and sign-bit keys."""
+    """Batches of many rows (more than 256 for keys of 256 values, 512 for 128, from 1536 for 64) are projected four rows to a
+    workgroup: the same bits as in a small batch, for cosine keys, their norms and sign-bit keys."""
     say(f"keys of {B} rows {dtype} d={d} k={k} S={S}")
     dt = torch.float32 if dtype == "f32" else torch.bfloat16
     g = torch.Generator(device="cuda").manual_seed(B)
@@ -1905,9 +1910,32 @@ def test_keys_of_many_rows_are_those_of_a_few(L, dtype, d, k, S, B):
         return fp, inv, bits
     for c in (None, bias):
         many = keys(h, c)
-        for rows in (slice(0, 9), slice(510, 515), slice(B - 6, B)):
+        for rows in (slice(0, 9), slice(B // 2, B // 2 + 5), slice(B - 6, B)):
             few = keys(h[rows].contiguous(), c)
             assert all(torch.equal(m[rows], f) for m, f in zip(many, few)), (rows, c is None)
+
+
+@pytest.mark.parametrize("dtype,d,k,n", [("bf16", 192, 256, 258), ("f32", 128, 128, 515), ("bf16", 64, 64, 1538)])
+def test_next_keys_of_a_large_bank_are_those_of_a_small_one(L, dtype, d, k, n):
+    """llmc_bank_pool_values projects the kept means of a large bank four rows to a workgroup: the bits of a small bank."""
+    say(f"next-layer keys of {n} stored values {dtype} d={d} k={k}")
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    g = torch.Generator(device="cuda").manual_seed(n)
+    act = torch.randn((n, 2, d), generator=g, device="cuda").to(dt)
+    P = (torch.randn((d, k), generator=g, device="cuda") * k ** -0.5).to(dt)
+    c = torch.randn((k,), generator=g, device="cuda") * 0.1
+
+    def keys(rows):
+        bank = L.Bank(rows.shape[0], 32, 2, d, dt, "cuda", keep_means=True, next_proj=P, next_bias=c)
+        bank.act.copy_(rows)
+        L.llmc_bank_pool_values(bank)
+        torch.cuda.synchronize()
+        out = [t.clone() for t in (bank.act_pool, bank.next_fp, bank.next_inv)]
+        bank.close()
+        return out
+    many = keys(act)
+    for rows in (slice(0, 5), slice(n - 3, n)):
+        assert all(torch.equal(m[rows], f) for m, f in zip(many, keys(act[rows]))), rows
 
 
 @pytest.mark.parametrize("dtype,d,S,B,n_bank,policy", [

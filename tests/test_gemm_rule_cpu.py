@@ -1,10 +1,6 @@
 """The tiling rule of the bf16 linear layers against measured times, and its tile counts."""
-import os
-import sys
-
 import pytest
 
-sys.path.insert(0, os.path.dirname(os.path.abspath(__file__)))
 import gemm_rule
 
 # rows, columns, K, an activation follows -> microseconds of the five tilings, each forced, one run on one MI355X
@@ -46,3 +42,21 @@ def test_the_rule_counts_the_tiles_of_its_choice(K):
                 bm, bn = sizes[gemm_rule.TILINGS[path]]
                 assert tiles == -(-M // bm) * -(-N // bn)
                 assert K > 64 or path >= 2                     # the ring starts with two steps
+
+
+def test_the_gpu_cases_reach_every_tiling_with_every_epilogue():
+    """The blocks that the GPU tests run: each takes the tilings that its row names, and together each tiling follows with no,
+    an activation and a residual; the two rings with a second tile a workgroup, also behind two steps of k."""
+    seen, second = set(), set()
+    for d, dff, S, B, tilings in gemm_rule.FEW_ROWS + gemm_rule.MANY_ROWS:
+        assert gemm_rule.block(d, dff, S * B) == tilings.split()
+        for t, n, k, epilogue in zip(tilings.split(), (3 * d, d, dff, d), (d, d, d, dff), ("plain", "residual", "act", "residual")):
+            seen.add((t, epilogue))
+            if gemm_rule.pick(S * B, n, k, epilogue == "act")[1] > 512:
+                second.add((t, epilogue))
+                if k == 128:
+                    second.add((t, epilogue, "two steps"))
+    assert seen == {(t, e) for t in gemm_rule.TILINGS for e in ("plain", "act", "residual")}
+    for t in ("128x192", "128x128"):
+        assert {(t, e) for e in ("plain", "act", "residual")} <= second
+    assert {("128x128", "plain", "two steps"), ("128x128", "act", "two steps")} <= second

@@ -11,6 +11,7 @@ import numpy as np
 import pytest
 import torch
 
+import gemm_rule
 from oracle import llmc_oracle as O
 from paper_2512_16843_amd import workloads as W
 
@@ -1997,19 +1998,12 @@ def test_few_rows_and_many_rows_give_the_same_bits(L, arch):
     big.close()
 
 
-@pytest.mark.parametrize("d,dff,S,B", [
-    (64, 64, 1, 1),          # one token, one step of k, one column tile
-    (64, 320, 31, 1),        # one row short of a tile; five steps of k in the second feed-forward layer
-    (192, 384, 33, 3),       # 99 tokens, three steps of k (less than the ring holds) and six (as many as it holds)
-    # seven and eleven steps, column counts that are odd multiples of 64; with one and seven steps (one more than a
-    # multiple of the ring's six stages) the epilogue's staging overwrites the very stage that the last step reads
-    (448, 704, 65, 2),
-    (768, 3072, 96, 12),     # 1152 tokens: two of the four layers take 32 x 64 tiles, the others 64 x 128
-])
+@pytest.mark.parametrize("d,dff,S,B,tilings", gemm_rule.FEW_ROWS)
 @pytest.mark.parametrize("arch", [0, 1])
-def test_bf16_layer_tilings(L, arch, d, dff, S, B):
+def test_bf16_layer_tilings(L, arch, d, dff, S, B, tilings):
     """The bf16 block on the tilings for few rows against the oracle, and the same bits for the last sequence computed
-    alone (where fewer rows may mean other tiles)."""
+    alone (where fewer rows may mean other tiles).  The case names the tilings that its layers take."""
+    assert gemm_rule.block(d, dff, S * B) == tilings.split()
     from paper_2512_16843_amd.engine import GatedStack
     say(f"plain bf16 layer arch={arch} d={d} dff={dff} S={S} B={B}")
     cfg = small_cfg(arch, "bf16", d, d // 64, dff, S, B)
@@ -2032,16 +2026,11 @@ def test_bf16_layer_tilings(L, arch, d, dff, S, B):
     one.close()
 
 
-@pytest.mark.parametrize("d,dff,S,B", [
-    (128, 320, 131, 130),    # 17,030 tokens, two steps of k (as many as the ring starts with), ragged column tiles
-    (448, 704, 97, 90),      # 8730 tokens, 26 in the last row of tiles; 1344, 448 and 704 columns in tiles of 192 and 128
-    (576, 1152, 67, 61),     # 4087 tokens: 64 x 128 and 64 x 64 tiles among the larger ones, nine and 18 steps
-    (1024, 4096, 128, 33),   # columns that divide by eight tiles, more tiles than workgroups
-])
+@pytest.mark.parametrize("d,dff,S,B,tilings", gemm_rule.MANY_ROWS)
 @pytest.mark.parametrize("arch", [0, 1])
-def test_bf16_layer_tilings_of_many_rows(L, arch, d, dff, S, B):
+def test_bf16_layer_tilings_of_many_rows(L, arch, d, dff, S, B, tilings):
     """The bf16 block on the tilings for many rows against the oracle, and the same bits for the last sequence alone."""
-    test_bf16_layer_tilings(L, arch, d, dff, S, B)
+    test_bf16_layer_tilings(L, arch, d, dff, S, B, tilings)
 
 
 @pytest.mark.parametrize("d,dff,S,B", [

@@ -25,9 +25,11 @@
 //   * the two lane halves exchange their maxima with one lane-swap instruction;
 //   * the row sum adds the ROUNDED probabilities, two per instruction, so the normaliser is
 //     the sum of exactly the weights the second product uses.
-// The chip holds 768 workgroups (148 registers), one per work item or several: 64 sequences of 384 tokens, 12 heads, 64.5 ->
-// 55.6 us with that many instead of 1024; causal, with single query blocks, longest first, instead of pairs of a long and a
-// short one: 8 sequences of 1024 tokens 41.6 -> 29.7 us (384 pairs left half the places empty).
+// The chip holds 768 workgroups (146 registers, 156 causal: three wavefronts a SIMD), one per work item or several.  Against
+// 1024 workgroups and, causal, items of a long and a short query block together (12 heads, us): not causal 64 sequences of
+// 384 tokens 63.6 -> 51.3, 16 of 1024 93.5 -> 75.8, 64, 128 and 256 of 128 unchanged (13, 22, 47); causal 8 of 1024 41.1 ->
+// 29.3 (384 pairs left half the places empty), 12 53.9 -> 41.1, 16 56.7 -> 54.6, 24 88.3 -> 80.3, 32 113 -> 105, 4 of 4096
+// 168 -> 165.
 #include "common.h"
 #include "mma.h"
 
@@ -43,8 +45,8 @@ struct AttnCfg {
 };
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-// 148 registers let a SIMD hold three wavefronts, so 768 workgroups are resident: larger jobs walk their items with a
-// grid stride (with 1024 workgroups the last 256 began when others had ended: four item times for three)
+// a SIMD holds three wavefronts, so 768 workgroups are resident: larger jobs walk their items with a grid stride (with 1024
+// workgroups the last 256 began when others had ended: four item times for three)
 constexpr int kMaxAttnGrid = 768;
 
 // maximum over the two lane halves (lane i and lane i ^ 32), in every lane
@@ -83,9 +85,11 @@ __global__ __launch_bounds__(AttnCfg::THREADS) void attention_mfma_kernel(const 
   const bf16x2_t ones = {(__bf16)1.0f, (__bf16)1.0f};
 
   for (int item = blockIdx.x; item < last; item += gridDim.x) {
-    // Causal: query block qb reads qb + 1 key blocks, so the longest blocks of all pairs come first and the shortest fill
-    // the gaps at the end.  Otherwise the blocks of a pair go to ONE of the eight XCDs that workgroups are dealt to in
-    // turn, so that its L2 fetches the pair's keys and values once.
+    // Causal: query block qb reads qb + 1 key blocks, so the longest blocks of all pairs come first.  Beyond 768 items the
+    // stride gives a workgroup with a longer block a longer one next round too (16 x 1024 tokens, 12 heads: 6 to 12 key blocks
+    // a workgroup where the pairs had 9 each), which takes back most of what the single blocks win there.  Otherwise the
+    // blocks of a pair go to ONE of the eight XCDs that workgroups are dealt to in turn, so that its L2 fetches the pair's
+    // keys and values once.
     int pair, qb;
     if (CAUSAL) {
       qb = n_qb - 1 - item / pairs;

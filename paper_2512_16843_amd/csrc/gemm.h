@@ -193,6 +193,12 @@ __device__ __forceinline__ void gemm_ring_tiles(const GemmArgs& g, int M, uint16
   // list, so that neighbouring tiles share their operand panels there: row by row for narrow outputs; wide outputs down
   // eight row blocks before the list moves one column tile on.  Where the column tiles divide by eight, plain striding
   // gives every XCD its own eighth of the columns instead: its L2 keeps those rows of W and only A streams.
+  // Each order forced on both tilings, blocks 64 to 2048 wide, geometric means over 2048 to 32,768 rows, against row by row:
+  // up to 8 column tiles grouped 0.98 to 1.04, strided 0.99 to 1.09 (two steps of k: 0.95 to 1.05); more, not divisible by
+  // eight, grouped 0.95 to 1.02, strided 0.95 to 1.09; divisible, strided / grouped 1.02 / 1.00 (128 x 192 tiles, 3072
+  // columns, K = 768), 1.00 / 0.97 (K = 1024), 0.95 / 0.99 (4608), 0.90 / 0.93 (6144), 0.93 / 0.95 (128 x 128, 4096), 0.98 /
+  // 0.94 (2048, K = 8192).  The rule is within 5 % of the best order in all of them, mostly within 2, which is what two runs
+  // differ by.
   const int order = tiles_n <= 8 ? 1 : tiles_n % 8 == 0 ? 0 : 2;
   const int xcd = blockIdx.x & 7, per_xcd = (total + 7) >> 3;
   const int it_step = order ? (int)(gridDim.x >> 3) : (int)gridDim.x;
@@ -538,7 +544,8 @@ __device__ __forceinline__ void gemm_step_tiles(const GemmArgs& g, int M, uint16
       for (int j = 0; j < C::FM; ++j) {
         uint16_t* dst[2];
 #pragma unroll
-        for (int p = 0; p < 2; ++p) dst[p] = out + map_row(g.o_rows, min(m + j * 32 + p * 16, M - 1), g.S, g.s_magic) * g.ldo + n;
+        for (int p = 0; p < 2; ++p)
+          dst[p] = out + map_row(g.o_rows, min(m + j * 32 + p * 16, M - 1), g.S, g.s_magic) * g.ldo + n;
 #pragma unroll
         for (int i = 0; i < C::FN; ++i) {
           float v[2][8];

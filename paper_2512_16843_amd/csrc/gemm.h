@@ -96,11 +96,11 @@ __device__ __forceinline__ float apply_act(float v, int act) {
 //
 // What bounds it: partly power, inferred from the clock (a loop of nothing but these matrix instructions on such values runs
 // at 1650 TFLOP/s and 1.7 GHz; with the fragment reads from LDS it reaches 1400, with the loads as well 950 to 1100).  Not it
-// alone: counters at 24,576 rows show the matrix pipe 35 to 37 % busy at 2.1 to 2.3 GHz and wavefronts waiting 40 to 49 % of
-// their cycles.  So bytes per flop count on every level even where their latency is hidden: a wavefront owns 64 x 96 outputs
-// (64 x 32 before: 1.8 times the bytes read from LDS), a compute unit two tiles of 128 x 192.  Then the epilogue, which only
-// the other workgroup's main loop covers: an activation chosen at compile time (GELU over 24,576 x 3072 outputs: 186 -> 145 us
-// for the layer).
+// alone: counters at 24,576 rows show the matrix pipe 35, 35 and 43 % busy (QKV, both feed-forward layers) at 2.1 to 2.3 GHz
+// and wavefronts waiting 40 to 52 % of their cycles.  So bytes per flop count on every level even where their latency is
+// hidden: a wavefront owns 64 x 96 outputs (64 x 32 before: 1.8 times the bytes read from LDS), a compute unit two tiles of
+// 128 x 192.  Then the epilogue, which only the other workgroup's main loop covers: an activation chosen at compile time (the
+// layer with GELU over 24,576 x 3072 outputs, all of it: 171 -> 155 us).
 // The four layers of a 768-wide block (microseconds, one run): eight wavefronts of 64 x 32 on 128 x 128 tiles / now: 32,768
 // rows 663 / 564, 24,576 rows 491 / 426, 10,240 rows 204 / 186, 8192 rows 180 / 168, 4096 rows 108 / 107, 2048 rows 73 / 66,
 // 788 rows 48 / 41, 128 rows 30 / 29; 4096 rows of 1024: 156 / 150.  Slower than those eight wavefronts: shallow products of

@@ -102,10 +102,10 @@ __device__ __forceinline__ float apply_act(float v, int act) {
 // 128 x 192.  Then the epilogue, which only the other workgroup's main loop covers: an activation chosen at compile time (the
 // layer with GELU over 24,576 x 3072 outputs, all of it: 171 -> 155 us).
 // The four layers of a 768-wide block (microseconds, one run): eight wavefronts of 64 x 32 on 128 x 128 tiles / now: 32,768
-// rows 663 / 564, 24,576 rows 491 / 426, 10,240 rows 204 / 186, 8192 rows 180 / 168, 4096 rows 108 / 107, 2048 rows 73 / 66,
-// 788 rows 48 / 41, 128 rows 30 / 29; 4096 rows of 1024: 156 / 150.  Slower than those eight wavefronts: shallow products of
-// many rows, where the epilogue of four wavefronts has less behind it to hide (128 wide: 24,576 rows 45 / 48, 32,768 rows
-// 51 / 54; 64 wide, 6144 rows and more: 2 to 3 %).
+// rows 639 / 563, 24,576 rows 481 / 420, 10,240 rows 206 / 189, 8192 rows 182 / 165, 4096 rows 105 / 105, 2048 rows 69 / 64,
+// 788 rows 47 / 40, 128 rows 30 / 29; 4096 rows of 1024: 154 / 148.  Slower than those eight wavefronts: shallow products of
+// many rows, where the epilogue of four wavefronts has less behind it to hide (128 wide: 24,576 rows 43 / 46, 32,768 rows
+// 50 / 53; 64 wide, 6144 rows and more, and 256 wide, 10,240 rows and more: 2 to 4 %).
 // Timed and not taken at 24,576 and 32,768 rows: 256 x 256 tiles with eight wavefronts of 128 x 64 and one workgroup to a
 // compute unit (within 2 % over 32,768 rows of 1024, where the tile count divides by 256, 20 to 60 % more elsewhere); steps of
 // 32 columns with three to five stages (64-byte rows of a panel: 7 to 20 % more); a third stage for A (4 % more).
@@ -589,7 +589,7 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_dma_kernel(GemmArgs g) {
   const int n_seq = g.count ? min(*g.count, g.max_seqs) : g.max_seqs;
   const int M = n_seq * g.S;
   if (M <= 0) return;
-  const GemmPick pick = gemm_pick(M, g.N, g.K / 64, EPI == kEpiGeluErf || EPI == kEpiGeluTanh);
+  const GemmPick pick = gemm_pick(M, g.N, g.K / 64, EPI == kEpiGeluErf || EPI == kEpiGeluTanh, EPI == kEpiResidual);
   const int busy = (pick.tiles + 7) & ~7;                // workgroups beyond have no tile, in any order of the tiles
   if ((int)blockIdx.x >= busy) {
     gemm_read_ahead(g, busy);

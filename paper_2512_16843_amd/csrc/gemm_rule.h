@@ -29,22 +29,22 @@ constexpr int kGemmFewRows = 1024;
 
 struct GemmPick { int path, tiles; };
 
-// M > 0 rows, N columns, nk steps of 64 columns of the operands; act: an activation follows the product.
+// M > 0 rows, N columns, nk steps of 64 columns of the operands; act, resid: an activation follows the product, a residual.
 //
 // The constants are fitted for the CHOICE, not for the time, to the four products of blocks 64 to 2048 wide (QKV, output
 // projection, both feed-forward layers) at 64 to 32,768 rows, each of the five tilings forced in turn in one process with
-// complete outputs (the same bits).  Of 616 products at 1280 rows and more the choice is 0.8 % slower than the fastest
+// complete outputs (the same bits).  Of 616 products at 1280 rows and more the choice is 0.7 % slower than the fastest
 // tiling in the mean, eight times more than 10 %, at most 15 %; one set of constants for all rows, fitted to widths of 256,
 // 768 and 1024, was 2.4 % slower in the mean, 55 times more than 10 %, up to 37 %, because it took 64 x 64 tiles where
-// 64 x 128 or the ring are faster: the four layers (us, before / now) of a block 128 wide at 24,576 rows 55.1 / 47.5, 256
-// wide at 8192 49.7 / 44.5, 384 wide at 8192 79.0 / 71.7, 512 wide at 6144 90.9 / 82.6, 768 wide at 2048 70.2 / 65.8, at 4096
-// 110.3 / 107.0 and at 8192 164.6 / 167.7 (128 x 128 and 128 x 192 tiles within 8 % at K = 3072: a tie lost).
+// 64 x 128 or the ring are faster: the four layers (us, before / now) of a block 128 wide at 24,576 rows 53.3 / 46.4, 256
+// wide at 8192 47.6 / 42.5, 384 wide at 8192 76.2 / 69.8, 512 wide at 6144 87.8 / 80.8, 768 wide at 2048 66.7 / 63.9, at 4096
+// 107.1 / 105.1 and at 8192 164.4 / 164.7.
 // Up to 1024 rows the constants are those of before without the ring, which won nothing there; few instructions count as
-// well, because such a launch runs through its code once, from a cold cache (128 rows of 768 29.7 / 29.2).
+// well, because such a launch runs through its code once, from a cold cache (128 rows of 768 29.2 / 29.1).
 // At 768 columns and K = 3072, 128 x 192 / 128 x 128 / 64 x 128 / 64 x 64 / 32 x 64 tiles take (us, one run) 126 / 144 / 167 /
 // 210 / 270 for 24,576 rows, 68 / 58 / 76 / 92 / 117 for 10,240, 49 / 53 / 59 / 71 / 94 for 8192, 43 / 38 / 36 / 36 / 48 for
 // 4096, 42 / 37 / 20 / 24 / 25 for 2048, 43 / 37 / 18 / 13 / 17 for 788, 44 / 37 / 17 / 12 / 11 for 256.
-LLMC_RULE GemmPick gemm_pick(int M, int N, int nk, bool act) {
+LLMC_RULE GemmPick gemm_pick(int M, int N, int nk, bool act, bool resid) {
   const int n64 = (N + 63) / 64, n128 = (n64 + 1) / 2, m64 = (M + 63) / 64, m32 = (M + 31) / 32;
   const int low_tiles = m64 * n128, tiny_tiles = m64 * n64, few_tiles = m32 * n64;
   GemmPick best = {kGemmLow, low_tiles};
@@ -63,7 +63,12 @@ LLMC_RULE GemmPick gemm_pick(int M, int N, int nk, bool act) {
   }
   const int n192 = (n64 + 2) / 3, m128 = (M + 127) / 128, big_tiles = m128 * n192, mid_tiles = m128 * n128;
   const int a = act ? 50 : 0;                          // alone, nothing covers a large tile's epilogue
-  const GemmCost big = {1021, 155, 564 + a, 129}, mid = {663, 122, 386 + a, 77};
+  // a long product with a residual follows one whose idle workgroups have read its weights: 128 x 192 tiles, one to a compute
+  // unit, against 128 x 128 tiles, two to some (us): 8192 x 768, K = 3072 49.0 / 52.9, 6144 x 768 45.7 / 48.9, 5120 x 1024,
+  // K = 4096 60.2 / 66.0, 4096 x 1280, K = 5120 87.2 / 88.8; of short ones 3072 x 1536, K = 1536 34.1 / 31.2, 2560 x 2048,
+  // K = 2048 42.0 / 40.1
+  const bool warm = resid && nk >= 40;
+  const GemmCost big = {1021, 155, (warm ? 574 : 564) + a, warm ? 123 : 129}, mid = {663, 122, 386 + a, 77};
   const bool ring = nk >= 2;                           // the ring starts with two steps
   if (ring && big_tiles > 4 * kGemmGrid) {             // many rounds: by the columns that are computed for padding
     const bool narrow = n192 * (big.both_fixed + nk * big.both_step) > n128 * (mid.both_fixed + nk * mid.both_step);

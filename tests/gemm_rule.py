@@ -17,8 +17,8 @@ def _lib():
         src, so = os.path.join(d, "rule.cpp"), os.path.join(d, "rule.so")
         with open(src, "w") as f:
             f.write('#include "gemm_rule.h"\n'
-                    'extern "C" void pick(int M, int N, int nk, int act, int* out) {\n'
-                    '  const llmc::GemmPick p = llmc::gemm_pick(M, N, nk, act != 0);\n'
+                    'extern "C" void pick(int M, int N, int nk, int act, int resid, int* out) {\n'
+                    '  const llmc::GemmPick p = llmc::gemm_pick(M, N, nk, act != 0, resid != 0);\n'
                     '  out[0] = p.path; out[1] = p.tiles;\n}\n')
         subprocess.run([os.environ.get("CXX", "g++"), "-std=c++17", "-O1", "-Wall", "-Werror", "-shared", "-fPIC", "-I", CSRC,
                         src, "-o", so], check=True)
@@ -27,16 +27,22 @@ def _lib():
         shutil.rmtree(d)
 
 
-def pick(M, N, K, act=False):
-    """(number of the tiling, tiles) that a launch of M rows, N columns and K steps of the contraction takes."""
+def pick(M, N, K, epilogue="plain"):
+    """(number of the tiling, tiles) that a launch of M rows and N columns contracted over K takes; the epilogue is "plain",
+    "act" or "residual"."""
     out = (ctypes.c_int * 2)()
-    _lib().pick(M, N, K // 64, int(act), out)
+    _lib().pick(M, N, K // 64, int(epilogue == "act"), int(epilogue == "residual"), out)
     return out[0], out[1]
 
 
 def block(d, dff, rows):
     """The tilings of a block's four linear layers (QKV, output projection, both feed-forward layers)."""
-    return [TILINGS[pick(rows, n, k, act)[0]] for n, k, act in ((3 * d, d, False), (d, d, False), (dff, d, True), (d, dff, False))]
+    return [TILINGS[pick(rows, n, k, e)[0]] for n, k, e in layers(d, dff)]
+
+
+def layers(d, dff):
+    """Columns, contraction and epilogue of a block's four linear layers."""
+    return [(3 * d, d, "plain"), (d, d, "residual"), (dff, d, "act"), (d, dff, "residual")]
 
 
 # Blocks (width, feed-forward width, tokens of a sequence, sequences) with the tilings that their four linear layers take: QKV,
@@ -57,5 +63,5 @@ MANY_ROWS = [
     (576, 1152, 67, 61, "128x128 64x128 64x128 64x128"),         # 4087 rows
     (576, 1152, 131, 229, "128x192 128x192 128x192 128x192"),    # 47 rows in the last row of tiles, second tiles with a residual
     (640, 1216, 131, 130, "128x128 128x128 128x192 128x128"),    # the same for 128 x 128; 1216 columns in tiles of 192
-    (1024, 4096, 128, 33, "128x128 64x128 128x192 128x128"),     # columns that divide by eight tiles
+    (1024, 4096, 128, 33, "128x128 64x128 128x192 128x192"),     # columns that divide by eight tiles
 ]
